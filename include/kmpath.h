@@ -104,10 +104,13 @@ extern "C" {
                           and replayed (those orders are launch-bound); the
                           graph's split-K factor is the one for all columns,
                           so results agree with eager launches to rounding  */
-#define KMP_FLAG_GLOBAL_SOLVE 2 /* keep the banded solve's working vector in
-                          device memory at every order (it is there anyway
-                          above the rows one workgroup's LDS holds: 20224
-                          padded rows on gfx950); results agree to rounding */
+#define KMP_FLAG_GLOBAL_SOLVE 2 /* every iteration in batched form with the
+                          banded solve's working vector in device memory at
+                          every order (it is there anyway above the rows one
+                          workgroup's LDS holds: 20224 padded rows on gfx950);
+                          otherwise, for padded orders up to 3072, the last
+                          columns of a stage go on with their dense
+                          resolvents; results agree to rounding            */
 
 /* Kernel classes timed with HIP events when their bit is set in
  * kmp_path_spec.timing_mask (1 << class). */
@@ -173,7 +176,11 @@ typedef struct {
 void kmp_default_spec(kmp_path_spec* spec);
 
 /* Bytes of DEVICE workspace kmp_fit_path needs for this problem when the
- * bandwidths are processed `sigma_batch` at a time (1 <= sigma_batch <= S).
+ * bandwidths are processed `sigma_batch` at a time (1 <= sigma_batch <= S),
+ * and, for padded orders up to 3072, at most 330 MB more for the dense
+ * resolvents of a stage's last columns. The latter part is optional: with a
+ * workspace too small for it every iteration runs in batched form (the size
+ * with KMP_FLAG_GLOBAL_SOLVE set is without it).
  * fold_id is HOST, n entries. Returns 0 if the arguments are invalid.     */
 size_t kmp_workspace_bytes(const kmp_path_spec* spec, int64_t n, int64_t d,
                            int32_t L, const int32_t* fold_id, int32_t V,

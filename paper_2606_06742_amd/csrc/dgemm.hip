@@ -851,6 +851,46 @@ int gemm_partial(hipStream_t s, const GemmArgs& g, bool a_kcontig, int S, double
   return 0;
 }
 
+// R = Q Y' of the dense columns for blocks of 64 rows of Y (block e =
+// e0 + blockIdx.y: column e / (N/64) of the list, rows 64 jb .. with jb =
+// e mod N/64, at Y + 64 N blockIdx.y): the tile (it, jb) of the symmetric R
+// for it >= jb, stored on both sides of the diagonal.
+__global__ __launch_bounds__(256) void resolvent_gemm_kernel(int N, int C, int e0,
+                                                             const double* __restrict__ Q,
+                                                             const DenseArrays a) {
+  const int nb = N / 64, e = e0 + (int)blockIdx.y, jb = e % nb, it = blockIdx.x;
+  const int tc = e / nb;
+  if (it < jb || tc >= *a.count) return;
+  const int g = a.list[tc] / C;
+  dbl4 acc[2][2];
+  tile_mainloop_vec<64, 16, true>(64, 0, N, 64 * it, 0, Q + (int64_t)g * N * N, N,
+                                  a.Y + (int64_t)blockIdx.y * 64 * N, N, nullptr, acc);
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int wi = (w & 1) * 32, wj = (w >> 1) * 32;
+  double* R = a.R + (int64_t)tc * N * N;
+#pragma unroll
+  for (int bi = 0; bi < 2; ++bi)
+#pragma unroll
+    for (int bj = 0; bj < 2; ++bj)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int i = 64 * it + wi + bi * 16 + mfma_row(lane, r);
+        const int j = 64 * jb + wj + bj * 16 + mfma_col(lane);
+        if (i >= j) {
+          R[(int64_t)i * N + j] = acc[bi][bj][r];
+          R[(int64_t)j * N + i] = acc[bi][bj][r];
+        }
+      }
+}
+
+int resolvent_gemm(hipStream_t s, int N, int C, int e0, int nblk, const double* Q,
+                   const DenseArrays& a) {
+  hipLaunchKernelGGL(resolvent_gemm_kernel, dim3((unsigned)(N / 64), (unsigned)nblk), dim3(256), 0, s,
+                     N, C, e0, Q, a);
+  KMP_LAUNCH_CHECK();
+  return 0;
+}
+
 int loss_epilogue(hipStream_t s, int M, int N, int batch, int S, const double* part, int64_t ldc,
                   int64_t sC, int64_t sP, double* Z, const LossEpi& e, const int* cmap,
                   const int* nact) {

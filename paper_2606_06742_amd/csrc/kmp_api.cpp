@@ -352,7 +352,7 @@ size_t carve(const Plan& p, void* ws, Layout* out) {
   l.flag = c.take<int>(cols);
   l.iters = c.take<int>(cols);
   l.iters_total = c.take<int>(cols);
-  l.active = c.take<int>(1);
+  l.active = c.take<int>(2);
   l.cmap = c.take<int>(cols);
   l.nact = c.take<int>(G);
   l.chk = c.take<int>(2);
@@ -375,6 +375,53 @@ size_t carve(const Plan& p, void* ws, Layout* out) {
   l.fold = c.take<int32_t>((size_t)p.n);
   if (out) *out = l;
   return c.off + kAlign;
+}
+
+// Dense columns (dense.hip): the area follows the workspace's fixed part and
+// is optional. A workspace that holds the fixed part only runs every
+// iteration in batched form. Its size is bounded: kDenseBytes of resolvents,
+// which the last-level cache holds.
+constexpr size_t kDenseBytes = (size_t)256 << 20;
+// Scratch while the resolvents are formed: blocks of 64 rows.
+constexpr size_t kDenseScratch = (size_t)64 << 20;
+int64_t dense_blocks(const Plan& p) {
+  return p.N <= kDenseSmall ? 0 : (int64_t)(kDenseScratch / (sizeof(double) * 64 * p.N));
+}
+
+size_t dense_column_bytes(const Plan& p) {
+  return sizeof(double) * ((size_t)p.N * p.N + (size_t)kDenseVectors * p.N + 2) + sizeof(int);
+}
+
+// Columns the area holds when `room` bytes are left for it.
+int dense_cap(const Plan& p, size_t room) {
+  const size_t fixed = 8 * kAlign + sizeof(double) * 64 * p.N * (size_t)dense_blocks(p);
+  if (p.N > kDenseMaxOrder || room <= fixed) return 0;
+  const size_t most = std::min(kDenseBytes, room - fixed) / dense_column_bytes(p);
+  return (int)std::min<size_t>(most, (size_t)p.G * p.C);
+}
+
+size_t dense_area_bytes(const Plan& p) {
+  const int cap = dense_cap(p, ~(size_t)0);
+  return cap > 0 ? cap * dense_column_bytes(p) + 8 * kAlign +
+                       sizeof(double) * 64 * p.N * (size_t)dense_blocks(p)
+                 : 0;
+}
+
+// The area inside the `room` bytes at base.
+DenseArrays carve_dense(const Plan& p, char* base, size_t room) {
+  DenseArrays a;
+  a.cap = dense_cap(p, room);
+  if (a.cap == 0) return a;
+  Carver c(base);
+  const size_t cap = a.cap, N = p.N;
+  a.R = c.take<double>(cap * N * N);
+  a.vec = c.take<double>(kDenseVectors * cap * N);
+  a.scal = c.take<double>(2 * cap);
+  a.list = c.take<int>(cap);
+  a.count = c.take<int>(1);
+  a.yblocks = dense_blocks(p);
+  a.Y = c.take<double>((size_t)a.yblocks * 64 * N);
+  return a;
 }
 
 int make_plan(const kmp_path_spec* spec, int64_t n, int64_t d, int32_t L, const int32_t* fold,
@@ -458,6 +505,35 @@ int make_plan(const kmp_path_spec* spec, int64_t n, int64_t d, int32_t L, const 
   p->RT = (int)ceil_div(p->N, kMinTileRows);
   p->bytes = carve(*p, nullptr, nullptr);
   return 0;
+}
+
+// Dense columns: iterations per launch up to kDenseSmall, iterations between
+// two polls above it, and checks that find f drifted before a stage goes back
+// to the batched iteration.
+constexpr int kDenseChunk = 4096, kDensePoll = 16, kDenseChecks = 3;
+// Whether a stage goes on in dense form from iteration `it` with `active`
+// columns in `groups` groups: once the batched iterations have taken what
+// forming the resolvents takes (they may be needed for few iterations more;
+// eight are granted), and above kDenseSmall for the logistic loss, whose
+// columns stop after tens of iterations (44 at most over 750 cells at n =
+// 2000, where two columns taken over near the end cost 0.5 of 21 ms), six
+// times that. Times in us, measured over orders 64 to 2048 and 1 to
+// 200 columns: a batched iteration takes 27 at order 64, 31 at 192, 57 at
+// 832, 82 at 1536 and 105 at 2048 (from there its two products read every
+// group's factors at 5 TB/s), a dense one 1.2 / 1.5 / 1.7 / 3.0 up to order
+// 256 and 256 columns, above 10 and the resolvents at 8 TB/s.
+bool dense_pays(int loss, int N, int groups, int it, int64_t active) {
+  const double n = N, k = (double)active;
+  const double batched = std::max(24.0 + 0.04 * n, groups * 16.0 * n * n / 5e6);
+  double dns, form;
+  if (N <= kDenseSmall) {
+    dns = 1.7 * (double)ceil_div(active, 256);
+    form = 120.0 + k * n * n * 2.5e-5;
+  } else {
+    dns = 9.0 + 0.003 * n + k * n * n * 1e-6;
+    form = (120.0 + 0.13 * n + k * n * n * n / 25e6) * (loss == KMP_LOGISTIC ? 6.0 : 1.0);
+  }
+  return (it + 8) * (batched - dns) >= form;
 }
 
 // Phase times from HIP events: mark() records an event on the stream (a
@@ -600,7 +676,8 @@ size_t kmp_workspace_bytes(const kmp_path_spec* spec, int64_t n, int64_t d, int3
   Plan p;
   if (sigma_batch < 1 || sigma_batch > S) return 0;
   if (make_plan(spec, n, d, L, fold_id, V, S, Q, sigma_batch, &p) != 0) return 0;
-  return p.bytes;
+  // (the device-memory solve at every order never takes the dense form)
+  return p.bytes + ((spec->flags & KMP_FLAG_GLOBAL_SOLVE) ? 0 : dense_area_bytes(p));
 }
 
 int kmp_rbf_gram(void* stream, const double* X, int64_t n, int64_t d, int64_t ldx,
@@ -800,6 +877,11 @@ int kmp_fit_path(void* stream, const kmp_path_spec* spec, const double* X, int64
   Layout lay;
   carve(plan, workspace, &lay);
   const int N = plan.N, C = plan.C, G = plan.G;
+  const DenseArrays dense =
+      (spec->flags & KMP_FLAG_GLOBAL_SOLVE)
+          ? DenseArrays{}
+          : carve_dense(plan, static_cast<char*>(workspace) + plan.bytes,
+                        workspace_bytes - plan.bytes);
   const size_t ncell = (size_t)S * Qn * V * L;
   // pinned staging for every host<->device transfer of the call
   const int nbatch = (S + Sb - 1) / Sb;
@@ -807,7 +889,7 @@ int kmp_fit_path(void* stream, const kmp_path_spec* spec, const double* X, int64
       Bump::round(sizeof(double) * n) + Bump::round(2 * sizeof(int)) +
       Bump::round(sizeof(int32_t) * (size_t)plan.nblk * N) +
       Bump::round(sizeof(int32_t) * (size_t)V * plan.Mh) + Bump::round(sizeof(int32_t) * n) +
-      Bump::round(sizeof(int) * ((size_t)G + 1)) +
+      Bump::round(sizeof(int) * ((size_t)G + 2)) +
       (size_t)nbatch * (Bump::round(sizeof(double) * Sb) +
                         2 * Bump::round(sizeof(double) * (size_t)G * C) +
                         2 * Bump::round(sizeof(int) * (size_t)G * C) +
@@ -927,7 +1009,7 @@ int kmp_fit_path(void* stream, const kmp_path_spec* spec, const double* X, int64
   struct PollBuf {
     int* p;
     hipEvent_t ev;
-  } poll{pin.take<int>((size_t)G + 1), ctx->ev_poll};
+  } poll{pin.take<int>((size_t)G + 2), ctx->ev_poll};
   // The first stage's factors need the band only: they are formed on a side
   // stream while the caller's stream accumulates Q, and the stage waits for
   // them. Leaving the call (also on an error) waits for the side stream.
@@ -1060,7 +1142,7 @@ int kmp_fit_path(void* stream, const kmp_path_spec* spec, const double* X, int64
       // converged, that iteration finds nothing to do and the stage ends).
       const auto post_poll = [&]() -> int {
         KMP_HIP_TRY(hipMemcpyAsync(poll.p, lay.nact, sizeof(int) * Gb, hipMemcpyDeviceToHost, s));
-        KMP_HIP_TRY(hipMemcpyAsync(poll.p + Gb, lay.active, sizeof(int), hipMemcpyDeviceToHost, s));
+        KMP_HIP_TRY(hipMemcpyAsync(poll.p + Gb, lay.active, 2 * sizeof(int), hipMemcpyDeviceToHost, s));
         KMP_HIP_TRY(hipEventRecord(poll.ev, s));
         return 0;
       };
@@ -1071,41 +1153,101 @@ int kmp_fit_path(void* stream, const kmp_path_spec* spec, const double* X, int64
         return 0;
       };
       const int restart = (spec->flags & KMP_FLAG_RESTART) ? 1 : 0;
-      IterGraph ig;
-      if (use_graphs && (rc = capture_iterations(pa, delta, kappa, spec->tol, spec->max_iter,
-                                                 restart, spec->poll_every, &ig)) != 0)
-        return rc;
-      if ((rc = post_poll()) != 0) return rc;
-      bool pending = true;
+      const auto poll_now = [&](int* active) -> int {
+        int r = path_compact(s, pa);
+        if (r == 0) r = post_poll();
+        return r != 0 ? r : read_poll(active);
+      };
       int it = 0;
-      while (it < spec->max_iter) {
-        if (ig.exec && it % spec->poll_every == 0 && it + spec->poll_every <= spec->max_iter) {
-          KMP_HIP_TRY(hipGraphLaunch(ig.exec, s));
-          it += spec->poll_every;
-        } else {
-          if ((rc = path_iteration(s, pa, delta, kappa, spec->tol, spec->max_iter, restart)) != 0)
-            return rc;
-          ++it;
-          // the active lists follow every iteration (one small launch), so
-          // the GEMMs drop a converged column at once; the counts still
-          // come back at the polls only
-          if (it % spec->poll_every != 0 && (rc = path_compact(s, pa)) != 0) return rc;
+      bool dense_on = dense.cap > 0, staged = false;
+      // Orders whose resolvent one compute unit holds: the whole stage in
+      // dense form, cap columns at a time; what a round leaves active (its
+      // launch's iterations used up, or f found drifted) begins again.
+      if (dense_on && N <= kDenseSmall && dense_pays(pa.loss, N, Gb, 0, (int64_t)Gb * C)) {
+        int active = Gb * C;
+        for (int round = 0; active > 0 && round < kDenseChecks + it / kDenseChunk; ++round) {
+          for (int b0 = 0; b0 < active; b0 += dense.cap) {
+            const int cols = std::min(dense.cap, active - b0);
+            if ((rc = dense_begin(s, pa, dense, b0, cols, delta, kappa, spec->tol)) != 0) return rc;
+            if ((rc = dense_iterations(s, pa, dense, cols, delta, kappa, spec->tol, spec->max_iter,
+                                       restart, kDenseChunk)) != 0)
+              return rc;
+            if ((rc = dense_check(s, pa, dense, cols, delta, kappa, spec->tol)) != 0) return rc;
+          }
+          if ((rc = poll_now(&active)) != 0) return rc;
+          it = poll.p[Gb + 1];
+        }
+        dense_on = false;
+        staged = active == 0;
+      }
+      if (!staged) {
+        IterGraph ig;
+        if (use_graphs && (rc = capture_iterations(pa, delta, kappa, spec->tol, spec->max_iter,
+                                                   restart, spec->poll_every, &ig)) != 0)
+          return rc;
+        if ((rc = post_poll()) != 0) return rc;
+        bool pending = true;
+        int dcols = 0, checks = 0;    // columns in dense form (0: the batched iteration)
+        while (it < spec->max_iter) {
+          if (dcols > 0) {
+            const int count = std::min(N <= kDenseSmall ? kDenseChunk : kDensePoll,
+                                       spec->max_iter - it);
+            if ((rc = dense_iterations(s, pa, dense, dcols, delta, kappa, spec->tol, spec->max_iter,
+                                       restart, count)) != 0)
+              return rc;
+            it += count;
+          } else if (ig.exec && it % spec->poll_every == 0 &&
+                     it + spec->poll_every <= spec->max_iter) {
+            KMP_HIP_TRY(hipGraphLaunch(ig.exec, s));
+            it += spec->poll_every;
+          } else {
+            if ((rc = path_iteration(s, pa, delta, kappa, spec->tol, spec->max_iter, restart)) != 0)
+              return rc;
+            ++it;
+            // the active lists follow every iteration (one small launch), so
+            // the GEMMs drop a converged column at once; the counts still
+            // come back at the polls only
+            if (it % spec->poll_every != 0 && (rc = path_compact(s, pa)) != 0) return rc;
+          }
+          if (pending) {
+            int active = 0;
+            if ((rc = read_poll(&active)) != 0) return rc;
+            pending = false;
+            if (active == 0 && dcols > 0) {
+              if ((rc = dense_check(s, pa, dense, dcols, delta, kappa, spec->tol)) != 0) return rc;
+              if ((rc = poll_now(&active)) != 0) return rc;
+              if (active > 0 && ++checks >= kDenseChecks) {   // back to the batched iteration
+                dcols = 0;
+                dense_on = false;
+              }
+            }
+            if (active == 0) {
+              dcols = 0;                                    // alpha is back in ahat
+              break;
+            }
+            const int groups = (int)(Gb - std::count(nact_h.begin(), nact_h.end(), 0));
+            if (dense_on && dcols == 0 && active <= dense.cap && dense_pays(pa.loss, N, groups, it, active)) {
+              if ((rc = path_compact(s, pa)) != 0) return rc;
+              if ((rc = dense_begin(s, pa, dense, 0, active, delta, kappa, spec->tol)) != 0) return rc;
+              dcols = active;
+            }
+          }
+          if (dcols > 0 || it % spec->poll_every == 0 || it >= spec->max_iter) {
+            if ((rc = path_compact(s, pa)) != 0) return rc;
+            if ((rc = post_poll()) != 0) return rc;
+            pending = true;
+          }
         }
         if (pending) {
           int active = 0;
           if ((rc = read_poll(&active)) != 0) return rc;
-          pending = false;
-          if (active == 0) break;
         }
-        if (it % spec->poll_every == 0 || it >= spec->max_iter) {
-          if ((rc = path_compact(s, pa)) != 0) return rc;
-          if ((rc = post_poll()) != 0) return rc;
-          pending = true;
-        }
-      }
-      if (pending) {
-        int active = 0;
-        if ((rc = read_poll(&active)) != 0) return rc;
+        // columns stopped by max_iter in dense form
+        if (dcols > 0 &&
+            (rc = dense_check(s, pa, dense, dcols, delta, kappa, spec->tol)) != 0)
+          return rc;
+        // (a launch of the register form runs no further than its columns)
+        if (dense.cap > 0 && N <= kDenseSmall) it = std::min(it, std::max(1, poll.p[Gb + 1]));
       }
       total_iters += it;
       if ((rc = tm.mark(s, &e6)) != 0) return rc;

@@ -217,7 +217,7 @@ struct PathArrays {
   int* flag = nullptr;      // 0 active, 1 converged, 2 max_iter, 3 non-finite
   int* iters = nullptr;     // per stage
   int* iters_total = nullptr;
-  int* active_count = nullptr;  // 1 int
+  int* active_count = nullptr;  // 2 ints
   int* cmap = nullptr;      // G x C: the active columns of each group, in order
   int* nact = nullptr;      // G: number of active columns of each group
   const int* nv_host = nullptr;  // G valid rows (host), for the work counters
@@ -233,13 +233,44 @@ int path_stage_vectors(hipStream_t s, const PathArrays& p, double kappa);
 int path_iteration(hipStream_t s, const PathArrays& p, double delta, double kappa, double tol,
                    int max_iter, int restart);
 // Rebuilds cmap/nact from the column flags and writes the total number of
-// active columns to active_count. The path GEMMs compute only the columns
+// active columns and the largest of the columns' iteration counts of the
+// stage to active_count (2 ints). The path GEMMs compute only the columns
 // listed in cmap, so it runs after every change of the flags that should
 // shrink the GEMMs (stage start, polls).
 int path_compact(hipStream_t s, const PathArrays& p);
 int group_ones_projection(hipStream_t s, const double* Q, const int* nv, int G, int N, double* cvec);
 // QB = Q B for G groups (Q, QB: N x N row-major each; band as in PathArrays).
 int form_qb(hipStream_t s, const double* Q, const double* band, int N, int G, double* QB);
+
+// The dense columns (dense.hip): cap columns' resolvents and vectors, and
+// scratch for yblocks blocks of 64 rows of N doubles while they are formed.
+struct DenseArrays {
+  int cap = 0;
+  double* R = nullptr;      // cap x N x N
+  double* vec = nullptr;    // kDenseVectors x cap x N
+  double* scal = nullptr;   // cap x 2
+  int* list = nullptr;      // cap: column of each
+  int* count = nullptr;     // 1
+  double* Y = nullptr;
+  int64_t yblocks = 0;
+};
+constexpr int kDenseVectors = 9;
+constexpr int kDenseMaxOrder = 3072;
+constexpr int kDenseSmall = 256;    // a column's resolvent fits one compute unit
+// dense_begin takes the active columns first .. first + cols - 1 (cols <=
+// cap) into dense form, dense_iterations runs count iterations of those still
+// active (orders up to kDenseSmall: in one launch). dense_check writes alpha
+// back into ahat, compares f with K alpha and lets a column whose f has
+// drifted go on.
+int dense_begin(hipStream_t s, const PathArrays& p, const DenseArrays& a, int first, int cols,
+                double delta, double kappa, double tol);
+int dense_iterations(hipStream_t s, const PathArrays& p, const DenseArrays& a, int cols, double delta,
+                     double kappa, double tol, int max_iter, int restart, int count);
+int dense_check(hipStream_t s, const PathArrays& p, const DenseArrays& a, int cols, double delta,
+                double kappa, double tol);
+// R = Q Y' for the nblk blocks of 64 rows of Y from block e0 (dgemm.hip).
+int resolvent_gemm(hipStream_t s, int N, int C, int e0, int nblk, const double* Q,
+                   const DenseArrays& a);
 
 // Exact hinge recovery after the smoothing stages (exact.hip): the buffers
 // of one bandwidth batch (cols = G*C columns of N rows).

@@ -1,0 +1,99 @@
+"""The dense form of a stage's last columns (dense.hip) against the batched
+iteration (KMP_FLAG_GLOBAL_SOLVE, which never takes it) on the same problem:
+the objective and coefficient bars of the oracle comparisons. Sizes lie on the
+edges of its variants: orders 64 to 256 (one compute unit per column), the
+first order above, odd sizes, and more columns than one area holds."""
+import numpy as np
+import pytest
+
+import workloads as W
+from tests.gpu_common import ALPHA_RTOL, CV_RTOL, OBJ_RTOL, announce, device
+
+pytestmark = pytest.mark.gpu
+
+
+def _both(inp, loss, ws=None, **kw):
+    from paper_2606_06742_amd import kmpath as km
+    device()
+    out = []
+    for flag in (0, km.KMP_FLAG_GLOBAL_SOLVE):
+        r = km.PathRunner(inp["X"], inp["y"], loss, inp["sigmas"], inp["lambdas"], inp["fold_id"],
+                          inp["V"], taus=inp["taus"] if loss == "check" else None, **kw)
+        r.spec.flags |= flag
+        if ws is not None:
+            r.ws_bytes = ws(r, km)
+        out.append((r.run(), r.results()))
+    return out
+
+
+def _agree(a, b):
+    (ca, ga), (cb, gb) = a, b
+    assert ca == cb and np.array_equal(ga["status"], gb["status"])
+    assert np.all(np.abs(ga["objective"] - gb["objective"]) <= OBJ_RTOL * np.abs(gb["objective"]))
+    scale = np.abs(gb["alpha"]).max(axis=-1, keepdims=True)
+    assert np.all(np.abs(ga["alpha"] - gb["alpha"]) <= ALPHA_RTOL * scale)
+    assert np.all(np.abs(ga["cv_sum"] - gb["cv_sum"]) <= CV_RTOL * np.maximum(1.0, gb["cv_sum"]))
+    assert np.array_equal(ga["selected"], gb["selected"])
+
+
+@pytest.mark.parametrize("loss,n,V,mode", [
+    ("hinge", 85, 4, {}),                    # order 64, one row short of it
+    ("check", 97, 3, {}),                    # order 128 (65 rows)
+    ("logistic", 191, 3, {}),
+    ("hinge", 233, 6, {}),                   # order 256
+    ("hinge", 256, 1, {"refit": True}),      # order 256, no padding
+    ("check", 257, 1, {"refit": True}),      # the first order above one compute unit
+    ("logistic", 601, 3, {}),
+    ("hinge", 701, 3, {}),
+    ("hinge", 190, 5, {"shared": True}),
+    ("check", 333, 4, {"shared": True}),
+])
+def test_dense_matches_batched(loss, n, V, mode):
+    inp = W.small_problem(loss, n, 5, seed=n, V=max(V, 2), L=7, lam_lo=-4.0, lam_hi=0.0)
+    announce(f"dense columns loss={loss} n={n} V={V} {mode}")
+    a, b = _both(inp, loss, **mode)
+    assert a[0] == 0
+    _agree(a, b)
+
+
+def test_dense_more_columns_than_the_area_holds():
+    """n = 190 leave-one-out: 190 x 6 columns of order 192 against 900 in the
+    area; the batched iteration first, then two areas' worth."""
+    inp = W.small_problem("hinge", 190, 4, seed=7, V=2, L=6, lam_lo=-3.0, lam_hi=0.0)
+    inp["fold_id"], inp["V"] = np.arange(190, dtype=np.int32), 190
+    announce("dense columns, leave-one-out n=190 L=6")
+    _agree(*_both(inp, "hinge", shared=True))
+
+
+def test_dense_needs_no_workspace():
+    """A workspace without the optional part runs batched iterations only, one
+    with part of it takes fewer columns: the same results to rounding."""
+    inp = W.small_problem("hinge", 150, 4, seed=8, V=3, L=5, lam_lo=-3.0, lam_hi=0.0)
+    sizes = []
+
+    def fixed(extra):
+        def size(r, km):
+            spec = km.kmp_default_spec("hinge", flags=r.spec.flags | km.KMP_FLAG_GLOBAL_SOLVE)
+            b = km.kmp_workspace_bytes(spec, 150, 4, 5, r.fold, 3, 1, 1, 1)
+            sizes.append((b, r.ws_bytes))
+            return b + extra
+        return size
+
+    announce("dense columns: workspace without the optional part")
+    for extra in (0, 400_000):
+        _agree(*_both(inp, "hinge", ws=fixed(extra)))
+    assert sizes[0][0] < sizes[0][1]
+
+
+@pytest.mark.parametrize("n,max_iter", [(100, 40), (100, 8), (500, 200), (500, 60)])
+def test_dense_stops_at_max_iter(n, max_iter):
+    """Columns that reach max_iter in dense form report it after exactly that
+    many iterations, as in batched form, from the same iterates."""
+    from paper_2606_06742_amd import kmpath as km
+    inp = W.small_problem("hinge", n, 4, seed=9, V=3, L=4, lam_lo=-5.0, lam_hi=-3.0)
+    announce(f"dense columns: max_iter={max_iter} n={n}")
+    (ca, a), (cb, b) = _both(inp, "hinge", max_iter=max_iter)
+    assert ca == cb == km.KMP_WMAXITER
+    assert np.array_equal(a["status"], b["status"]) and np.array_equal(a["iters"], b["iters"])
+    scale = np.abs(b["alpha"]).max(axis=-1, keepdims=True)
+    assert np.all(np.abs(a["alpha"] - b["alpha"]) <= ALPHA_RTOL * scale)

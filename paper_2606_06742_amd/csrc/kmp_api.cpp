@@ -147,34 +147,6 @@ static int capture_iterations(const PathArrays& pa, double delta, double kappa, 
 
 namespace {
 
-// Device scratch of the allocation-free Gram entry point: the bandwidth
-// factors (8 doubles) and the squared row norms of X (up to
-// kStaticScratchDoubles - 8 rows). Each device holds its own copy for the
-// life of the process; host code reaches it only through the address
-// hipGetSymbolAddress returns on that device (static_scratch below).
-constexpr size_t kStaticScratchDoubles = (size_t)1 << 16;   // 512 KiB
-static __device__ __align__(256) double scratch[kStaticScratchDoubles];
-
-int static_scratch(double** out) {
-  int dev = 0;
-  KMP_HIP_TRY(hipGetDevice(&dev));
-  static std::mutex mu;
-  static std::map<int, double*> ptrs;
-  std::lock_guard<std::mutex> lk(mu);
-  auto it = ptrs.find(dev);
-  if (it == ptrs.end()) {
-    void* p = nullptr;
-    KMP_HIP_TRY(hipGetSymbolAddress(&p, HIP_SYMBOL(scratch)));
-    if (!p) {
-      set_error("static scratch has no device address");
-      return KMP_EHIP;
-    }
-    it = ptrs.emplace(dev, static_cast<double*>(p)).first;
-  }
-  *out = it->second;
-  return 0;
-}
-
 // A second stream per device for work that can run beside the caller's
 // stream (joined back through events); created on first use and kept for
 // the life of the process, at the default priority.
@@ -289,7 +261,7 @@ struct Layout {
   double *spart, *pnext, *band, *bpart, *gram_all, *tmat_all, *cross_all, *xpart;
   double *ahat, *abar, *zmat, *anew, *estep, *ldl_l, *ldl_d, *vhat, *uvec, *partial, *fpart, *zpart;
   double *ldl_lr, *ldl_dr, *twist, *band_rev;
-  double *beta, *bbar, *rmom, *gcoef, *kkt, *lam, *taucol, *fbuf, *nrm, *inv2s2;
+  double *beta, *bbar, *rmom, *gcoef, *kkt, *lam, *taucol, *fbuf;
   int *flag, *iters, *iters_total, *active, *nvg, *chk, *cmap, *nact, *stat_count, *cnv;
   int32_t *tidx, *hidx, *fold, *rfold, *cfold;
   // exact hinge recovery (only with KMP_FLAG_EXACT_HINGE)
@@ -347,8 +319,6 @@ size_t carve(const Plan& p, void* ws, Layout* out) {
   l.lam = c.take<double>(cols);
   l.taucol = c.take<double>(cols);
   l.fbuf = c.take<double>(cols * (size_t)p.Mh);
-  l.nrm = c.take<double>((size_t)p.n);
-  l.inv2s2 = c.take<double>((size_t)std::max(p.S, 1));
   l.flag = c.take<int>(cols);
   l.iters = c.take<int>(cols);
   l.iters_total = c.take<int>(cols);
@@ -680,73 +650,49 @@ size_t kmp_workspace_bytes(const kmp_path_spec* spec, int64_t n, int64_t d, int3
   return p.bytes + ((spec->flags & KMP_FLAG_GLOBAL_SOLVE) ? 0 : dense_area_bytes(p));
 }
 
-int kmp_rbf_gram(void* stream, const double* X, int64_t n, int64_t d, int64_t ldx,
-                 const int32_t* rows, int64_t m, const int32_t* cols, int64_t p,
-                 const double* sigmas, int32_t S, double* out, int64_t ld_out) {
-  hipStream_t s = (hipStream_t)stream;
+// Both Gram entry points (`name` for the messages).
+static int gram_call(const char* name, hipStream_t s, const double* X, int64_t n, int64_t d,
+                     int64_t ldx, const int32_t* rows, int64_t m, const int32_t* cols, int64_t p,
+                     const double* sigmas, int32_t S, double* out, int64_t ld_out,
+                     int64_t max_rows) {
   if (!X || !rows || !cols || !sigmas || !out || n < 1 || d < 1 || ldx < d || m < 0 || p < 0 ||
       S < 1 || S > 8 || ld_out < p) {
-    set_error("kmp_rbf_gram: invalid arguments");
+    set_error(std::string(name) + ": invalid arguments");
     return KMP_EINVAL;
   }
-  std::vector<double> f2(S);
-  for (int i = 0; i < S; ++i) {
-    if (!(sigmas[i] > 0.0) || !std::isfinite(sigmas[i])) {
-      set_error("kmp_rbf_gram: sigma must be positive");
-      return KMP_EINVAL;
-    }
-    f2[i] = 1.0 / (2.0 * sigmas[i] * sigmas[i]);
-  }
-  if (m == 0 || p == 0) return KMP_OK;
-  double *nrm = nullptr, *dinv = nullptr;
-  KMP_HIP_TRY(hipMallocAsync((void**)&nrm, sizeof(double) * n, s));
-  KMP_HIP_TRY(hipMallocAsync((void**)&dinv, sizeof(double) * S, s));
-  KMP_HIP_TRY(hipMemcpyAsync(dinv, f2.data(), sizeof(double) * S, hipMemcpyHostToDevice, s));
-  int rc = row_norms(s, X, n, d, ldx, nrm);
-  if (rc == 0)
-    rc = rbf_blocks(s, X, d, ldx, nrm, rows, 0, m, cols, 0, p, 1, dinv, S, out, m * ld_out, 0,
-                    ld_out);
-  KMP_HIP_TRY(hipFreeAsync(nrm, s));
-  KMP_HIP_TRY(hipFreeAsync(dinv, s));
-  KMP_HIP_TRY(hipStreamSynchronize(s));
-  return rc;
-}
-
-int kmp_rbf_gram_noalloc(void* stream, const double* X, int64_t n, int64_t d, int64_t ldx,
-                         const int32_t* rows, int64_t m, const int32_t* cols, int64_t p,
-                         const double* sigmas, int32_t S, double* out, int64_t ld_out) {
-  hipStream_t s = (hipStream_t)stream;
-  if (!X || !rows || !cols || !sigmas || !out || n < 1 || d < 1 || ldx < d || m < 0 || p < 0 ||
-      S < 1 || S > 8 || ld_out < p) {
-    set_error("kmp_rbf_gram_noalloc: invalid arguments");
-    return KMP_EINVAL;
-  }
-  if ((size_t)n > kStaticScratchDoubles - 8) {
-    set_error("kmp_rbf_gram_noalloc: n = " + std::to_string(n) + " above the " +
-              std::to_string(kStaticScratchDoubles - 8) + " rows its static scratch holds");
+  if (n > max_rows) {
+    set_error(std::string(name) + ": n = " + std::to_string(n) + " above the " +
+              std::to_string(max_rows) + " rows its static scratch held");
     return KMP_EINVAL;
   }
   double f2[8];
   for (int i = 0; i < S; ++i) {
     if (!(sigmas[i] > 0.0) || !std::isfinite(sigmas[i])) {
-      set_error("kmp_rbf_gram_noalloc: sigma must be positive");
+      set_error(std::string(name) + ": sigma must be positive");
       return KMP_EINVAL;
     }
     f2[i] = 1.0 / (2.0 * sigmas[i] * sigmas[i]);
   }
   if (m == 0 || p == 0) return KMP_OK;
-  double* sc = nullptr;
-  int rc = static_scratch(&sc);
+  const int rc =
+      rbf_blocks(s, X, d, ldx, rows, 0, m, cols, 0, p, 1, f2, S, out, m * ld_out, 0, ld_out);
   if (rc != 0) return rc;
-  double* dinv = sc;          // S bandwidth factors
-  double* nrm = sc + 8;       // n squared row norms
-  if ((rc = store_small(s, f2, S, dinv)) != 0) return rc;
-  if ((rc = row_norms(s, X, n, d, ldx, nrm)) != 0) return rc;
-  if ((rc = rbf_blocks(s, X, d, ldx, nrm, rows, 0, m, cols, 0, p, 1, dinv, S, out, m * ld_out, 0,
-                       ld_out)) != 0)
-    return rc;
   KMP_HIP_TRY(hipStreamSynchronize(s));
   return KMP_OK;
+}
+
+int kmp_rbf_gram(void* stream, const double* X, int64_t n, int64_t d, int64_t ldx,
+                 const int32_t* rows, int64_t m, const int32_t* cols, int64_t p,
+                 const double* sigmas, int32_t S, double* out, int64_t ld_out) {
+  return gram_call("kmp_rbf_gram", (hipStream_t)stream, X, n, d, ldx, rows, m, cols, p, sigmas, S,
+                   out, ld_out, INT64_MAX);
+}
+
+int kmp_rbf_gram_noalloc(void* stream, const double* X, int64_t n, int64_t d, int64_t ldx,
+                         const int32_t* rows, int64_t m, const int32_t* cols, int64_t p,
+                         const double* sigmas, int32_t S, double* out, int64_t ld_out) {
+  return gram_call("kmp_rbf_gram_noalloc", (hipStream_t)stream, X, n, d, ldx, rows, m, cols, p,
+                   sigmas, S, out, ld_out, 65528);
 }
 
 int kmp_tridiag(void* stream, double* A, int32_t G, int32_t N, double* Qout, double* diag,
@@ -890,8 +836,7 @@ int kmp_fit_path(void* stream, const kmp_path_spec* spec, const double* X, int64
       Bump::round(sizeof(int32_t) * (size_t)plan.nblk * N) +
       Bump::round(sizeof(int32_t) * (size_t)V * plan.Mh) + Bump::round(sizeof(int32_t) * n) +
       Bump::round(sizeof(int) * ((size_t)G + 2)) +
-      (size_t)nbatch * (Bump::round(sizeof(double) * Sb) +
-                        2 * Bump::round(sizeof(double) * (size_t)G * C) +
+      (size_t)nbatch * (2 * Bump::round(sizeof(double) * (size_t)G * C) +
                         2 * Bump::round(sizeof(int) * (size_t)G * C) +
                         Bump::round(sizeof(int) * (size_t)G)) +
       Bump::round(sizeof(int32_t) * (size_t)G * N) +
@@ -1026,7 +971,6 @@ int kmp_fit_path(void* stream, const kmp_path_spec* spec, const double* X, int64
   side.done = ctx->ev_fact;
   size_t ev_start = 0, e1 = 0, e2 = 0, e3 = 0;
   if ((rc = tm.mark(s, &ev_start)) != 0) return rc;
-  if ((rc = row_norms(s, X, n, d, ldx, lay.nrm)) != 0) return rc;
 
   PathArrays pa = path_arrays_of(lay, plan, spec->loss, (spec->flags & KMP_FLAG_GLOBAL_SOLVE) != 0);
   const bool use_graphs = (spec->flags & KMP_FLAG_EAGER) == 0 && N <= kGraphMaxOrder &&
@@ -1040,7 +984,7 @@ int kmp_fit_path(void* stream, const kmp_path_spec* spec, const double* X, int64
     // c = (tau, lambda). Shared factor: group g = bandwidth, column
     // c = (tau, fold, lambda), rows held out of the column's fold carry no
     // loss, and each column keeps its fold's n_v as loss normaliser.
-    double* f2 = pin.take<double>(Sb);
+    double f2[8];
     double* lamc = pin.take<double>((size_t)G * C);
     double* tauc = pin.take<double>((size_t)G * C);
     int* nvg = pin.take<int>(G);
@@ -1059,7 +1003,6 @@ int kmp_fit_path(void* stream, const kmp_path_spec* spec, const double* X, int64
         cfh[(size_t)g * C + c] = shared ? v : -1;
       }
     }
-    KMP_HIP_TRY(hipMemcpyAsync(lay.inv2s2, f2, sizeof(double) * sb, hipMemcpyHostToDevice, s));
     KMP_HIP_TRY(hipMemcpyAsync(lay.lam, lamc, sizeof(double) * (size_t)Gb * C,
                                hipMemcpyHostToDevice, s));
     KMP_HIP_TRY(hipMemcpyAsync(lay.taucol, tauc, sizeof(double) * (size_t)Gb * C,
@@ -1085,7 +1028,7 @@ int kmp_fit_path(void* stream, const kmp_path_spec* spec, const double* X, int64
     // a1: Gram + fold gather into A (group g = s_local*V + v)
     if ((rc = tm.mark(s, &e1)) != 0) return rc;
     kc_begin(KMP_KC_GRAM, s);
-    if ((rc = rbf_blocks(s, X, d, ldx, lay.nrm, lay.tidx, N, N, lay.tidx, N, N, NB, lay.inv2s2, sb,
+    if ((rc = rbf_blocks(s, X, d, ldx, lay.tidx, N, N, lay.tidx, N, N, NB, f2, sb,
                          lay.A, (int64_t)NB * N * N, (int64_t)N * N, N)) != 0)
       return rc;
     {
@@ -1257,9 +1200,9 @@ int kmp_fit_path(void* stream, const kmp_path_spec* spec, const double* X, int64
 
     // a10: finalize
     FinalArgs fa;
-    fa.n = (int)n; fa.d = (int)d; fa.ldx = ldx; fa.X = X; fa.nrm = lay.nrm; fa.y = y;
+    fa.n = (int)n; fa.d = (int)d; fa.ldx = ldx; fa.X = X; fa.y = y;
     fa.fold = lay.fold; fa.tidx = lay.tidx; fa.V = V; fa.S_b = sb; fa.Qt = Qn; fa.L = L;
-    fa.s0 = s0; fa.S = S; fa.inv2s2 = lay.inv2s2; fa.delta = delta_final; fa.fbuf = lay.fbuf;
+    fa.s0 = s0; fa.S = S; fa.inv2s2 = f2; fa.delta = delta_final; fa.fbuf = lay.fbuf;
     fa.hidx = lay.hidx; fa.Mh = plan.Mh; fa.kh = lay.A; fa.ftrain = lay.fpart;
     fa.alpha = alpha; fa.beta_out = beta; fa.objective = objective; fa.cv_sum = cv_sum;
     fa.shared = shared;

@@ -73,22 +73,18 @@ int loss_epilogue(hipStream_t s, int M, int N, int batch, int S, const double* p
 // out[0], out[1] = counts of non-finite entries of X (n x d, ldx) and y (n).
 int count_nonfinite(hipStream_t s, const double* X, int64_t n, int64_t d, int64_t ldx,
                     const double* y, int* out);
-// Squared row norms of X (n x d, ldx): nrm[i] = sum_k X[i][k]^2.
-int row_norms(hipStream_t s, const double* X, int64_t n, int64_t d, int64_t ldx, double* nrm);
-
-// Up to 8 doubles passed by value to a one-wavefront kernel that stores them
-// at out (device).
+// Up to 8 doubles passed to a kernel by value.
 struct Small8 {
   double v[8];
 };
-int store_small(hipStream_t s, const double* vals, int count, double* out);
 
 // For each of `nb` index blocks (blockIdx.z = block q), rows idx_r + q*sr,
 // cols idx_c + q*sc (m and p entries, negative = padding), write for each of
-// S bandwidths: out + (s*sout_s + q*sout_q) + i*ld + j.
-int rbf_blocks(hipStream_t s, const double* X, int64_t d, int64_t ldx, const double* nrm,
-               const int32_t* idx_r, int64_t sr, int64_t m,
-               const int32_t* idx_c, int64_t sc, int64_t p, int nb,
+// S bandwidths (inv2s2: S host values 1/(2 sigma^2), S <= 8):
+// out + (s*sout_s + q*sout_q) + i*ld + j. One list for rows and columns
+// (idx_r == idx_c, m == p) gives a symmetric matrix.
+int rbf_blocks(hipStream_t s, const double* X, int64_t d, int64_t ldx, const int32_t* idx_r,
+               int64_t sr, int64_t m, const int32_t* idx_c, int64_t sc, int64_t p, int nb,
                const double* inv2s2, int S, double* out, int64_t sout_s, int64_t sout_q,
                int64_t ld);
 
@@ -314,13 +310,13 @@ int exact_commit(hipStream_t s, const ExactArgs& x, double* alpha_loc, double* f
 // counts of cells that hit max_iter or went non-finite.
 struct FinalArgs {
   int n = 0, d = 0; int64_t ldx = 0;
-  const double* X = nullptr; const double* nrm = nullptr; const double* y = nullptr;
+  const double* X = nullptr; const double* y = nullptr;
   const int32_t* fold = nullptr;   // n fold ids (device)
   const int32_t* tidx = nullptr;   // V x N training indices (-1 pad)
   const int32_t* hidx = nullptr;   // V x Mh held-out indices (-1 pad)
   int Mh = 0;                      // padded held-out rows per fold (<= N)
   int V = 0, S_b = 0, Qt = 1, L = 0, s0 = 0, S = 0;
-  const double* inv2s2 = nullptr;  // S_b bandwidth factors of this batch
+  const double* inv2s2 = nullptr;  // S_b bandwidth factors of this batch (host)
   double delta = 1.0;
   double* kh = nullptr;            // G x N x N: training, then held-out kernel blocks (ld N)
   double* ftrain = nullptr;        // G x C x N training predictions (without beta)

@@ -1935,7 +1935,7 @@ static int path_finalize_shared(hipStream_t s, const PathArrays& p, const FinalA
   hipLaunchKernelGGL(mask_heldout_kernel, dim3((unsigned)ceil_div(p.N, 256), (unsigned)cols),
                      dim3(256), 0, s, p.N, p.C, p.rfold, p.cfold, p.zmat);
   KMP_LAUNCH_CHECK();
-  if ((rc = rbf_blocks(s, fa.X, fa.d, fa.ldx, fa.nrm, fa.tidx, p.N, p.N, fa.tidx, p.N, p.N, 1,
+  if ((rc = rbf_blocks(s, fa.X, fa.d, fa.ldx, fa.tidx, p.N, p.N, fa.tidx, p.N, p.N, 1,
                        fa.inv2s2, fa.S_b, fa.kh, (int64_t)p.N * p.N, (int64_t)p.N * p.N, p.N)) != 0)
     return rc;
   GemmArgs gt = g;
@@ -1974,7 +1974,7 @@ int path_finalize(hipStream_t s, const PathArrays& p, const FinalArgs& fa) {
   // training predictions K_v alpha in observation space: K_v is built again
   // from X into the factor buffer (no longer needed) and multiplied by
   // alpha, so the objective does not carry the factorisation's rounding
-  if ((rc = rbf_blocks(s, fa.X, fa.d, fa.ldx, fa.nrm, fa.tidx, p.N, p.N, fa.tidx, p.N, p.N,
+  if ((rc = rbf_blocks(s, fa.X, fa.d, fa.ldx, fa.tidx, p.N, p.N, fa.tidx, p.N, p.N,
                        fa.V, fa.inv2s2, fa.S_b, fa.kh, (int64_t)fa.V * p.N * p.N,
                        (int64_t)p.N * p.N, p.N)) != 0)
     return rc;
@@ -1987,7 +1987,7 @@ int path_finalize(hipStream_t s, const PathArrays& p, const FinalArgs& fa) {
   // held-out kernel blocks K[H_v, T_v] (into the same buffer), then held-out
   // predictions K[H_v, T_v] alpha (none in a refit)
   if (fa.Mh > 0 &&
-      (rc = rbf_blocks(s, fa.X, fa.d, fa.ldx, fa.nrm, fa.hidx, fa.Mh, fa.Mh, fa.tidx, p.N, p.N,
+      (rc = rbf_blocks(s, fa.X, fa.d, fa.ldx, fa.hidx, fa.Mh, fa.Mh, fa.tidx, p.N, p.N,
                        fa.V, fa.inv2s2, fa.S_b, fa.kh, (int64_t)fa.V * p.N * p.N,
                        (int64_t)p.N * p.N, p.N)) != 0)
     return rc;

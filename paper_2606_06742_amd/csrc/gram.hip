@@ -80,34 +80,29 @@ constexpr int GT = 64, GK = 16, GPAD = 4, MAXS = 8;
 // consecutive k of one row): the lanes of one store land in distinct banks.
 __device__ __forceinline__ int gcol(int k, int c) { return c ^ (((k >> 2) & 3) << 2); }
 
-// Features gk .. gk + 3 of one point, zero past d or for a padding point (its
-// pointer is any valid row's).
+// Features gk .. gk + 3 of one point; those past d repeat others (zeroed when
+// they are staged).
 template <bool PAIRS>
-__device__ __forceinline__ void gram_fetch(const double* __restrict__ x, bool point, int64_t gk,
-                                           int64_t d, double (&r)[4]) {
+__device__ __forceinline__ void gram_fetch(const double* __restrict__ x, int64_t gk, int64_t d,
+                                           double (&r)[4]) {
   if constexpr (PAIRS) {
 #pragma unroll
-    for (int u = 0; u < 4; u += 2) {
-      const bool ok = gk + u < d;                  // d even: the pair is in or out
-      const double2 a = *reinterpret_cast<const double2*>(x + (ok ? gk + u : 0));
-      r[u] = ok && point ? a.x : 0.0;
-      r[u + 1] = ok && point ? a.y : 0.0;
+    for (int u = 0; u < 4; u += 2) {               // d even: a pair is in or out
+      const double2 a = *reinterpret_cast<const double2*>(x + min(gk + u, d - 2));
+      r[u] = a.x;
+      r[u + 1] = a.y;
     }
   } else {
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const bool ok = gk + u < d;
-      const double a = x[ok ? gk + u : 0];
-      r[u] = ok && point ? a : 0.0;
-    }
+    for (int u = 0; u < 4; ++u) r[u] = x[min(gk + u, d - 1)];
   }
 }
 
 // One 64 x 64 tile per workgroup, wave w the 32 x 32 quadrant (32 (w&1),
 // 32 (w>>1)); X in slices of 16 features through two LDS stages, the next
 // slice's loads in flight during the products of the current one (no branch
-// around a load: rows and features past the end read row 0 or feature 0 and
-// are zeroed). PAIRS: d and ldx even and X 16-byte aligned, so a row's
+// around a load and no arithmetic on it before it is staged: rows and features
+// past the end read valid ones and are zeroed there). PAIRS: d and ldx even and X 16-byte aligned, so a row's
 // features load as pairs. SYM: rows and columns are one list, so the matrix
 // is symmetric: the tiles on and below the diagonal are computed and stored
 // on both sides, through LDS in whole row pieces (straight from the
@@ -148,16 +143,18 @@ __global__ __launch_bounds__(256, 4) void rbf_blocks_kernel(
   const double* pc = X + (int64_t)(xc >= 0 ? xc : 0) * ldx;
   double ra[4], rb[4], sr2 = 0.0, sc2 = 0.0;
   const auto fetch = [&](int64_t k0) {
-    gram_fetch<PAIRS>(pr, xr >= 0, k0 + kb, d, ra);
-    gram_fetch<PAIRS>(pc, xc >= 0, k0 + kb, d, rb);
+    gram_fetch<PAIRS>(pr, k0 + kb, d, ra);
+    gram_fetch<PAIRS>(pc, k0 + kb, d, rb);
   };
-  const auto store = [&](int st) {
+  const auto store = [&](int st, int64_t k0) {
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      As[st][kb + u][gcol(kb + u, row)] = ra[u];
-      Bs[st][kb + u][gcol(kb + u, row)] = rb[u];
-      sr2 = fma(ra[u], ra[u], sr2);
-      sc2 = fma(rb[u], rb[u], sc2);
+      const bool in = k0 + kb + u < d;
+      const double a = in && xr >= 0 ? ra[u] : 0.0, b = in && xc >= 0 ? rb[u] : 0.0;
+      As[st][kb + u][gcol(kb + u, row)] = a;
+      Bs[st][kb + u][gcol(kb + u, row)] = b;
+      sr2 = fma(a, a, sr2);
+      sc2 = fma(b, b, sc2);
     }
   };
   dbl4 acc[2][2];
@@ -166,7 +163,7 @@ __global__ __launch_bounds__(256, 4) void rbf_blocks_kernel(
 #pragma unroll
     for (int b = 0; b < 2; ++b) acc[a][b] = dbl4{0.0, 0.0, 0.0, 0.0};
   fetch(0);
-  store(0);
+  store(0, 0);
   __syncthreads();
   const int64_t nk = (d + GK - 1) / GK;
   for (int64_t kt = 0; kt < nk; ++kt) {
@@ -185,7 +182,7 @@ __global__ __launch_bounds__(256, 4) void rbf_blocks_kernel(
       acc[1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b1, acc[1][1], 0, 0, 0);
     }
     if (more) {
-      store(cur ^ 1);
+      store(cur ^ 1, (kt + 1) * GK);
       __syncthreads();
     }
   }

@@ -1364,13 +1364,7 @@ int kmp_dgemm_grouped(void* stream, int32_t G, int32_t M, int32_t N, int32_t K, 
     KMP_HIP_TRY(hipStreamSynchronize(s));
     return KMP_OK;
   }
-  GemmArgs g;
-  g.M = M; g.N = N; g.K = K; g.batch = G;
-  g.A = A; g.lda = K; g.sA = (int64_t)M * K;
-  g.B = B; g.ldb = N; g.sB = (int64_t)K * N;
-  g.C = C; g.ldc = N; g.sC = (int64_t)M * N;
-  g.alpha = 1.0; g.beta = 0.0;
-  int rc = gemm(s, g, true, false, true);
+  const int rc = grouped_product(s, G, M, N, K, A, B, C);
   if (rc != 0) return rc;
   KMP_HIP_TRY(hipStreamSynchronize(s));
   return KMP_OK;

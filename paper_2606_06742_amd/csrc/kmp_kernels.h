@@ -69,6 +69,10 @@ int loss_epilogue(hipStream_t s, int M, int N, int batch, int S, const double* p
                   int64_t sC, int64_t sP, double* Z, const LossEpi& e, const int* cmap,
                   const int* nact);
 
+// C_b = A_b B_b for b < G, row-major and packed (product.hip); M, N, K >= 1.
+int grouped_product(hipStream_t s, int G, int M, int N, int K, const double* A, const double* B,
+                    double* C);
+
 // ---------------------------------------------------------------- Gram
 // out[0], out[1] = counts of non-finite entries of X (n x d, ldx) and y (n).
 int count_nonfinite(hipStream_t s, const double* X, int64_t n, int64_t d, int64_t ldx,

@@ -14,16 +14,12 @@
 // tests do not change under the orthogonal Q). f is compared with K alpha
 // through the factor when the columns have stopped (dense_check).
 //
-// Up to order kDenseSmall a column's whole stage runs in one workgroup with R
-// in its registers; above, an iteration is two launches: the products of all
-// dense columns spread over the chip, then one workgroup per column for
-// everything elementwise. An iteration of 48 columns in 4 groups, batched and
-// dense: order 64 27 and 1.1 us, 192 31 and 1.6 us, 256 33 and 3.4 us, 320
-// 36 and 13 us, 832 (16 columns) 58 and 22 us, 1536 (4 columns) 81 and 22 us.
-// Up to order 256 it is bound by the three barriers and the sums between
-// them, above by the two launches and then by reading R (8 TB/s from the
-// last-level cache). n = 200, 5 folds x 10 penalties, hinge: 77.9 -> 5.8 ms
-// per call.
+// An iteration is two launches: the products of all dense columns spread over
+// the chip, then one workgroup per column for everything elementwise. An
+// iteration of some columns in 4 groups, batched and dense: order 320, 48
+// columns 36 and 13 us, 832, 16 columns 58 and 22 us, 1536, 4 columns 81 and
+// 22 us. It is bound by the two launches and then by reading R (8 TB/s from
+// the last-level cache). (Up to order kSmallOrder see small.hip.)
 #include "kmp_common.h"
 #include "kmp_kernels.h"
 
@@ -65,21 +61,21 @@ __device__ __forceinline__ void block_sum3(double& x, double& y, double& z, doub
   }
 }
 
-// The dense columns: the active columns first .. first + cap - 1, counted
-// group by group in the order of the active lists (one wavefront).
-__global__ __launch_bounds__(64) void dense_list_kernel(int G, int C, int first, int cap,
+// The dense columns: every active column, group by group in the order of the
+// active lists (one wavefront).
+__global__ __launch_bounds__(64) void dense_list_kernel(int G, int C, int cap,
                                                         const int* __restrict__ cmap,
                                                         const int* __restrict__ nact,
                                                         int* __restrict__ list,
                                                         int* __restrict__ count) {
-  int base = -first;
+  int base = 0;
   for (int g = 0; g < G; ++g) {
     const int n = nact[g];
     for (int k = threadIdx.x; k < n; k += 64)
-      if (base + k >= 0 && base + k < cap) list[base + k] = g * C + cmap[(int64_t)g * C + k];
+      if (base + k < cap) list[base + k] = g * C + cmap[(int64_t)g * C + k];
     base += n;
   }
-  if (threadIdx.x == 0) *count = max(0, min(base, cap));
+  if (threadIdx.x == 0) *count = min(base, cap);
 }
 
 // Y = Q M^{-1} by rows (M = 2 lambda I + B/(n_v kappa) of a column, from its
@@ -446,251 +442,6 @@ __global__ __launch_bounds__(DT) void dense_check_kernel(const DenseArrays a, co
   if (threadIdx.x == 0) p.flag[gc] = 0;
 }
 
-// Orders up to kDenseSmall. R = Y Q' in place: a wavefront multiplies its own
-// 16 rows of Y, read whole before they are overwritten. Both operands are
-// rows along k: lane group lk takes k = 16 c + 4 lk + s in MFMA step s, 32
-// contiguous bytes of each row.
-template <int NT>
-__global__ __launch_bounds__(256) void dense_small_gemm_kernel(int C, const DenseArrays a,
-                                                               const double* __restrict__ Q) {
-  constexpr int N = 16 * NT, nb = N / 64;
-  const int t = (int)blockIdx.x / nb;
-  if (t >= *a.count) return;
-  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
-  const double* q = Q + (int64_t)(a.list[t] / C) * N * N + (int64_t)li * N + 4 * lk;
-  double* y = a.R + ((int64_t)blockIdx.x * 64 + 16 * w) * N;
-  ddbl4 acc[NT];
-#pragma unroll
-  for (int j = 0; j < NT; ++j) acc[j] = ddbl4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll 1
-  for (int k = 0; k < N; k += 16) {
-    const double2* yr = reinterpret_cast<const double2*>(y + (int64_t)li * N + 4 * lk + k);
-    const double2 a01 = yr[0], a23 = yr[1];
-#pragma unroll
-    for (int j = 0; j < NT; ++j) {
-      const double2* qr = reinterpret_cast<const double2*>(q + (int64_t)16 * j * N + k);
-      const double2 b01 = qr[0], b23 = qr[1];
-      acc[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a01.x, b01.x, acc[j], 0, 0, 0);
-      acc[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a01.y, b01.y, acc[j], 0, 0, 0);
-      acc[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a23.x, b23.x, acc[j], 0, 0, 0);
-      acc[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a23.y, b23.y, acc[j], 0, 0, 0);
-    }
-  }
-#pragma unroll
-  for (int j = 0; j < NT; ++j)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) y[(int64_t)(4 * r + lk) * N + 16 * j + li] = acc[j][r];
-}
-
-// Sum over the wavefront in every lane: rotations within the rows of 16
-// lanes, then the permlane swaps.
-template <int R>
-__device__ __forceinline__ double row_ror(double v) {
-  const long long b = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_mov_dpp((int)b, 0x120 + R, 0xf, 0xf, false);
-  const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), 0x120 + R, 0xf, 0xf, false);
-  return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
-}
-__device__ __forceinline__ double fast_wave_sum(double v) {
-  v += row_ror<8>(v);
-  v += row_ror<4>(v);
-  v += row_ror<2>(v);
-  v += row_ror<1>(v);
-  {
-    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
-    const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)b, (unsigned)b, false, false);
-    const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(b >> 32), (unsigned)(b >> 32), false, false);
-    v = __longlong_as_double((long long)(((unsigned long long)hi[0] << 32) | lo[0])) +
-        __longlong_as_double((long long)(((unsigned long long)hi[1] << 32) | lo[1]));
-  }
-  const unsigned long long b = (unsigned long long)__double_as_longlong(v);
-  const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)b, (unsigned)b, false, false);
-  const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(b >> 32), (unsigned)(b >> 32), false, false);
-  return __longlong_as_double((long long)(((unsigned long long)hi[0] << 32) | lo[0])) +
-         __longlong_as_double((long long)(((unsigned long long)hi[1] << 32) | lo[1]));
-}
-
-// Up to `count` iterations of one column per workgroup (order N = 64 NR), the
-// same steps as dense_product_kernel and dense_update_kernel with nothing
-// leaving the compute unit: wavefront w keeps columns CW w .. of R, lane l the
-// rows l, l + 64, .., in registers (the last CL of them in LDS at NR = 4,
-// where the registers hold no more); w is read from LDS as a broadcast and
-// the wavefronts' partial products are added through LDS by thread i < N,
-// which owns row i. Three barriers per iteration: w and its sums, the
-// partial products, the restart test. LOSS is the loss code: fixed, so that
-// the registers hold nothing for the other losses.
-template <int NR, int LOSS>
-__global__ __launch_bounds__(DT) void dense_small_kernel(const DenseArrays a, const PathArrays p,
-                                                         double delta, double kappa, double tol,
-                                                         int max_iter, int restart, int count) {
-  constexpr int N = 64 * NR, CW = N / DW, CL = NR == 4 ? 8 : 0, CR = CW - CL;
-  __shared__ double ws[N];
-  __shared__ double xp[DW][N];
-  __shared__ double red[NR][3], red1[NR];
-  __shared__ double rl[CL > 0 ? DW * CL : 1][CL > 0 ? N : 1];
-  __shared__ double own_lds[5][CL > 0 ? N : 1];   // the owner's v, K v, y, alpha, f at NR = 4
-  const int t = blockIdx.x;
-  if (t >= *a.count) return;
-  const int64_t gc = a.list[t];
-  if (p.flag[gc] != 0) return;                    // uniform over the block
-  const int tid = threadIdx.x, wv = tid >> 6, lane = tid & 63;
-  const int g = (int)(gc / p.C), nv = p.nv[g];
-  const double lam2 = 2.0 * p.lam[gc], nvd = (double)p.cnv[gc], tau = p.tau[gc];
-  const double nk = nvd * kappa, gco = p.gcoef[gc];
-  // R is symmetric: its row c holds column c contiguously
-  double rr[NR][CR];
-  const double* R = a.R + (int64_t)t * N * N + (int64_t)(CW * wv) * N + lane;
-#pragma unroll
-  for (int c = 0; c < CR; ++c)
-#pragma unroll
-    for (int q = 0; q < NR; ++q) rr[q][c] = R[c * N + 64 * q];
-#pragma unroll
-  for (int c = 0; c < CL; ++c)
-#pragma unroll
-    for (int q = 0; q < NR; ++q) rl[CL * wv + c][64 * q + lane] = R[(CR + c) * N + 64 * q];
-  const bool own = tid < N, valid = tid < nv;
-  const int i = own ? tid : 0;
-  double reg[5];
-  const auto mine = [&](int k) -> double& {
-    if constexpr (CL > 0) return own_lds[k][i];
-    else return reg[k];
-  };
-  if (own) {
-    mine(0) = dvec(a, N, VV, t)[i];
-    mine(1) = dvec(a, N, VKV, t)[i];
-    mine(2) = p.ylab[(int64_t)g * N + i];
-    mine(3) = dvec(a, N, VA, t)[i];
-    mine(4) = dvec(a, N, VF, t)[i];
-  }
-  double ab = dvec(a, N, VAB, t)[i], fb = dvec(a, N, VFB, t)[i], w = dvec(a, N, VW, t)[i];
-  const bool live = valid && !(p.rfold && p.rfold[(int64_t)g * N + i] == p.cfold[gc]);
-  double d0 = a.scal[2 * t], tv = a.scal[2 * t + 1];
-  double beta = p.beta[gc], bb = p.bbar[gc], rm = p.rmom[gc], kkt = p.kkt[gc];
-  const int it0 = p.iters[gc];
-  int it = it0, fl = 0;
-  if (own) ws[tid] = w;
-  __syncthreads();
-  for (int n = 0; n < count; ++n) {
-    // x = R w: the wavefront's columns
-    double s[NR];
-#pragma unroll
-    for (int q = 0; q < NR; ++q) s[q] = 0.0;
-#pragma unroll
-    for (int c = 0; c < CR; c += 2) {
-      const double2 wc = *reinterpret_cast<const double2*>(&ws[CW * wv + c]);
-#pragma unroll
-      for (int q = 0; q < NR; ++q) s[q] = fma(rr[q][c + 1], wc.y, fma(rr[q][c], wc.x, s[q]));
-      // at NR = 4 no registers are left to read w far ahead
-      if constexpr (CL > 0) __builtin_amdgcn_sched_barrier(0);
-    }
-#pragma unroll
-    for (int c = 0; c < CL; ++c) {
-#pragma unroll
-      for (int q = 0; q < NR; ++q)
-        s[q] = fma(rl[CL * wv + c][64 * q + lane], ws[CW * wv + CR + c], s[q]);
-      if constexpr (CL > 0) __builtin_amdgcn_sched_barrier(0);
-    }
-#pragma unroll
-    for (int q = 0; q < NR; ++q) xp[wv][64 * q + lane] = s[q];
-    // the momentum without a restart needs nothing of this step
-    const double rn1 = 0.5 * (1.0 + sqrt(1.0 + 4.0 * rm * rm));
-    const double co1 = (rn1 - 1.0) / (0.5 * (1.0 + sqrt(1.0 + 4.0 * rn1 * rn1)));
-    const double sa = gco * (tv - d0), db = gco * (d0 - tv);
-    const double bn = bb - db;
-    __syncthreads();
-    double ea = 0.0, ef = 0.0, rd = 0.0;
-    if (wv < NR) {
-      double x = 0.0;
-#pragma unroll
-      for (int j = 0; j < DW; ++j) x += xp[j][tid];
-      if (valid) {
-        const double da = fma(sa, mine(0), x);
-        ab -= da;
-        fb -= fma(sa, mine(1), nk * fma(-lam2, x, w));
-        ea = ab - mine(3);
-        ef = fb - mine(4);
-        rd = da * ea;
-      }
-      rd = fast_wave_sum(rd);
-      if (lane == 0) red1[wv] = rd;
-    }
-    __syncthreads();
-    rd = db * (bn - beta);
-#pragma unroll
-    for (int j = 0; j < NR; ++j) rd += red1[j];
-    const bool turn = restart && rd > 0.0;
-    const double coef = turn ? 0.0 : co1;
-    rm = turn ? 1.0 : rn1;
-    if (valid) {
-      mine(3) = ab;
-      mine(4) = fb;
-    }
-    ab = fma(coef, ea, ab);
-    fb = fma(coef, ef, fb);
-    bb = fma(coef, bn - beta, bn);
-    beta = bn;
-    if (++it >= max_iter) {
-      fl = 2;
-      break;
-    }
-    double zs = 0.0, n2 = 0.0, tw = 0.0;
-    if (wv < NR) {
-      if (valid) {
-        zs = live ? loss_psi(LOSS, mine(2), fb + bb, delta, tau) / nvd : 0.0;
-        w = fma(lam2, ab, zs);
-        n2 = w * w;
-        tw = mine(1) * w;
-        ws[tid] = w;
-      }
-      zs = fast_wave_sum(zs);
-      n2 = fast_wave_sum(n2);
-      tw = fast_wave_sum(tw);
-      if (lane == 0) {
-        red[wv][0] = zs;
-        red[wv][1] = n2;
-        red[wv][2] = tw;
-      }
-    }
-    __syncthreads();
-    d0 = tv = n2 = 0.0;
-#pragma unroll
-    for (int j = 0; j < NR; ++j) {
-      d0 += red[j][0];
-      n2 += red[j][1];
-      tv += red[j][2];
-    }
-    kkt = nvd * fmax(sqrt(n2), fabs(d0));
-    if (!(n2 == n2) || !(d0 == d0) || !(kkt <= 1e300)) {
-      fl = 3;
-      break;
-    }
-    if (kkt <= tol) {                             // certified at the extrapolated point
-      fl = 1;
-      if (valid) mine(3) = ab;
-      beta = bb;
-      break;
-    }
-  }
-  if (own) {
-    dvec(a, N, VA, t)[i] = mine(3);
-    dvec(a, N, VAB, t)[i] = ab;
-    dvec(a, N, VF, t)[i] = mine(4);
-    dvec(a, N, VFB, t)[i] = fb;
-    dvec(a, N, VW, t)[i] = w;
-  }
-  if (tid == 0) {
-    a.scal[2 * t] = d0;
-    a.scal[2 * t + 1] = tv;
-    p.beta[gc] = beta;
-    p.bbar[gc] = bb;
-    p.rmom[gc] = rm;
-    p.kkt[gc] = kkt;
-    p.iters[gc] = it;
-    p.iters_total[gc] += it - it0;
-    if (fl != 0) p.flag[gc] = fl;
-  }
-}
-
 template <bool START>
 int launch_update(hipStream_t s, const PathArrays& p, const DenseArrays& a, int cols, double delta,
                   double kappa, double tol, int max_iter, int restart) {
@@ -712,36 +463,20 @@ int launch_update(hipStream_t s, const PathArrays& p, const DenseArrays& a, int 
 }
 }  // namespace
 
-int dense_begin(hipStream_t s, const PathArrays& p, const DenseArrays& a, int first, int cols,
-                double delta, double kappa, double tol) {
+int dense_begin(hipStream_t s, const PathArrays& p, const DenseArrays& a, int cols, double delta,
+                double kappa, double tol) {
   int rc;
   const int N = p.N, nb = N / 64;
-  hipLaunchKernelGGL(dense_list_kernel, dim3(1), dim3(64), 0, s, p.G, p.C, first, cols, p.cmap,
-                     p.nact, a.list, a.count);
+  hipLaunchKernelGGL(dense_list_kernel, dim3(1), dim3(64), 0, s, p.G, p.C, cols, p.cmap, p.nact,
+                     a.list, a.count);
   KMP_LAUNCH_CHECK();
   const int64_t blocks = (int64_t)cols * nb;
-  if (N <= kDenseSmall) {
-    hipLaunchKernelGGL(dense_rows_kernel, dim3((unsigned)blocks), dim3(256), 0, s, N, p.C, 0, a, p.Q,
-                       p.ldl_l, p.ldl_d, a.R);
+  for (int64_t e0 = 0; e0 < blocks; e0 += a.yblocks) {
+    const int nblk = (int)std::min<int64_t>(a.yblocks, blocks - e0);
+    hipLaunchKernelGGL(dense_rows_kernel, dim3((unsigned)nblk), dim3(256), 0, s, N, p.C, (int)e0, a,
+                       p.Q, p.ldl_l, p.ldl_d, a.Y);
     KMP_LAUNCH_CHECK();
-#define KMP_SMALL_CASE(NR)                                                                       \
-  if (N == 64 * NR)                                                                              \
-    hipLaunchKernelGGL((dense_small_gemm_kernel<4 * NR>), dim3((unsigned)blocks), dim3(256), 0, s, \
-                       p.C, a, p.Q);
-    KMP_SMALL_CASE(1)
-    KMP_SMALL_CASE(2)
-    KMP_SMALL_CASE(3)
-    KMP_SMALL_CASE(4)
-#undef KMP_SMALL_CASE
-    KMP_LAUNCH_CHECK();
-  } else {
-    for (int64_t e0 = 0; e0 < blocks; e0 += a.yblocks) {
-      const int nblk = (int)std::min<int64_t>(a.yblocks, blocks - e0);
-      hipLaunchKernelGGL(dense_rows_kernel, dim3((unsigned)nblk), dim3(256), 0, s, N, p.C, (int)e0, a,
-                         p.Q, p.ldl_l, p.ldl_d, a.Y);
-      KMP_LAUNCH_CHECK();
-      if ((rc = resolvent_gemm(s, N, p.C, (int)e0, nblk, p.Q, a)) != 0) return rc;
-    }
+    if ((rc = resolvent_gemm(s, N, p.C, (int)e0, nblk, p.Q, a)) != 0) return rc;
   }
   hipLaunchKernelGGL((dense_vectors_kernel<false>), dim3((unsigned)(N / 4), (unsigned)cols), dim3(256),
                      0, s, N, p.C, a, p.Q, p.QB, p.nv, p.ahat, p.abar, p.vhat, p.uvec);
@@ -752,29 +487,8 @@ int dense_begin(hipStream_t s, const PathArrays& p, const DenseArrays& a, int fi
 int dense_iterations(hipStream_t s, const PathArrays& p, const DenseArrays& a, int cols, double delta,
                      double kappa, double tol, int max_iter, int restart, int count) {
   int rc = 0;
-  // the resolvent and 14 vectors of each column and iteration (the register
-  // form reads them once)
+  // the resolvent and 14 vectors of each column
   const double n = (double)p.N, flops = cols * (2.0 * n * n + 24.0 * n);
-  if (p.N <= kDenseSmall) {
-    kc_begin(KMP_KC_UPDATE, s);
-#define KMP_SMALL_CASE(NR, LS)                                                                   \
-  if (p.N == 64 * NR && p.loss == LS)                                                            \
-    hipLaunchKernelGGL((dense_small_kernel<NR, LS>), dim3((unsigned)cols), dim3(DT), 0, s, a, p, \
-                       delta, kappa, tol, max_iter, restart, count);
-#define KMP_SMALL_CASES(LS) \
-  KMP_SMALL_CASE(1, LS)     \
-  KMP_SMALL_CASE(2, LS)     \
-  KMP_SMALL_CASE(3, LS)     \
-  KMP_SMALL_CASE(4, LS)
-    KMP_SMALL_CASES(0)
-    KMP_SMALL_CASES(1)
-    KMP_SMALL_CASES(2)
-#undef KMP_SMALL_CASES
-#undef KMP_SMALL_CASE
-    KMP_LAUNCH_CHECK();
-    kc_end(KMP_KC_UPDATE, s, 8.0 * cols * (n * n + 14.0 * n), flops);
-    return 0;
-  }
   for (int k = 0; k < count && rc == 0; ++k) {
     kc_begin(KMP_KC_UPDATE, s);
     hipLaunchKernelGGL(dense_product_kernel, dim3((unsigned)ceil_div(p.N, 2 * DW), (unsigned)cols),

@@ -355,7 +355,7 @@ constexpr size_t kDenseBytes = (size_t)256 << 20;
 // Scratch while the resolvents are formed: blocks of 64 rows.
 constexpr size_t kDenseScratch = (size_t)64 << 20;
 int64_t dense_blocks(const Plan& p) {
-  return p.N <= kDenseSmall ? 0 : (int64_t)(kDenseScratch / (sizeof(double) * 64 * p.N));
+  return (int64_t)(kDenseScratch / (sizeof(double) * 64 * p.N));
 }
 
 size_t dense_column_bytes(const Plan& p) {
@@ -365,7 +365,7 @@ size_t dense_column_bytes(const Plan& p) {
 // Columns the area holds when `room` bytes are left for it.
 int dense_cap(const Plan& p, size_t room) {
   const size_t fixed = 8 * kAlign + sizeof(double) * 64 * p.N * (size_t)dense_blocks(p);
-  if (p.N > kDenseMaxOrder || room <= fixed) return 0;
+  if (p.N <= kSmallOrder || p.N > kDenseMaxOrder || room <= fixed) return 0;
   const size_t most = std::min(kDenseBytes, room - fixed) / dense_column_bytes(p);
   return (int)std::min<size_t>(most, (size_t)p.G * p.C);
 }
@@ -477,32 +477,25 @@ int make_plan(const kmp_path_spec* spec, int64_t n, int64_t d, int32_t L, const 
   return 0;
 }
 
-// Dense columns: iterations per launch up to kDenseSmall, iterations between
-// two polls above it, and checks that find f drifted before a stage goes back
+// Small orders: iterations of a column per launch. Dense columns: iterations
+// between two polls, and checks that find f drifted before a stage goes back
 // to the batched iteration.
-constexpr int kDenseChunk = 4096, kDensePoll = 16, kDenseChecks = 3;
+constexpr int kSmallChunk = 8192, kDensePoll = 16, kDenseChecks = 3;
 // Whether a stage goes on in dense form from iteration `it` with `active`
 // columns in `groups` groups: once the batched iterations have taken what
 // forming the resolvents takes (they may be needed for few iterations more;
-// eight are granted), and above kDenseSmall for the logistic loss, whose
-// columns stop after tens of iterations (44 at most over 750 cells at n =
-// 2000, where two columns taken over near the end cost 0.5 of 21 ms), six
-// times that. Times in us, measured over orders 64 to 2048 and 1 to
-// 200 columns: a batched iteration takes 27 at order 64, 31 at 192, 57 at
-// 832, 82 at 1536 and 105 at 2048 (from there its two products read every
-// group's factors at 5 TB/s), a dense one 1.2 / 1.5 / 1.7 / 3.0 up to order
-// 256 and 256 columns, above 10 and the resolvents at 8 TB/s.
+// eight are granted), and for the logistic loss, whose columns stop after tens
+// of iterations (44 at most over 750 cells at n = 2000, where two columns taken
+// over near the end cost 0.5 of 21 ms), six times that. Times in us, measured
+// over orders 320 to 2048 and 1 to 200 columns: a batched iteration takes 35 at
+// order 320, 57 at 832, 82 at 1536 and 105 at 2048 (from there its two products
+// read every group's factors at 5 TB/s), a dense one 10 and the resolvents at
+// 8 TB/s.
 bool dense_pays(int loss, int N, int groups, int it, int64_t active) {
   const double n = N, k = (double)active;
   const double batched = std::max(24.0 + 0.04 * n, groups * 16.0 * n * n / 5e6);
-  double dns, form;
-  if (N <= kDenseSmall) {
-    dns = 1.7 * (double)ceil_div(active, 256);
-    form = 120.0 + k * n * n * 2.5e-5;
-  } else {
-    dns = 9.0 + 0.003 * n + k * n * n * 1e-6;
-    form = (120.0 + 0.13 * n + k * n * n * n / 25e6) * (loss == KMP_LOGISTIC ? 6.0 : 1.0);
-  }
+  const double dns = 9.0 + 0.003 * n + k * n * n * 1e-6;
+  const double form = (120.0 + 0.13 * n + k * n * n * n / 25e6) * (loss == KMP_LOGISTIC ? 6.0 : 1.0);
   return (it + 8) * (batched - dns) >= form;
 }
 
@@ -1039,34 +1032,95 @@ int kmp_fit_path(void* stream, const kmp_path_spec* spec, const double* X, int64
       kc_end(KMP_KC_GRAM, s, 8.0 * sb * e2, 2.0 * d * e2);
     }
     if ((rc = tm.mark(s, &e2)) != 0) return rc;
-    // a2: factorisation
-    BandWork bw = band_work_of(lay, Gb, N, nvg);
-    bw.band_ready = side.band;
-    if ((rc = band_reduce(s, bw)) != 0) return rc;
-    if ((rc = form_qb(s, lay.Qm, lay.band, N, Gb, lay.A)) != 0) return rc;
-    KMP_HIP_TRY(hipStreamWaitEvent(side.st, side.band, 0));
-    side.queued = true;
-    if ((rc = path_stage_factor(side.st, pa, stage_kappa(0))) != 0) return rc;
-    KMP_HIP_TRY(hipEventRecord(side.done, side.st));
-    if ((rc = group_ones_projection(s, lay.Qm, lay.nvg, Gb, N, lay.cvec)) != 0) return rc;
     if ((rc = gather_labels(s, y, lay.tidx, NB, sb, N, lay.ylab)) != 0) return rc;
     if ((rc = path_init_columns(s, pa)) != 0) return rc;
-    if ((rc = tm.mark(s, &e3)) != 0) return rc;
-    tm.span(&t_gram, e1, e2);
-    tm.span(&t_factor, e2, e3);
-
-    if (s0 == 0) {
-      // the inputs' checks have long come back (the factorisation is
-      // queued ahead of the device); on an error the queued work drains
-      // into the workspace only
-      if ((rc = check_inputs()) != 0) {
+    const auto first_checks = [&]() -> int {
+      if (s0 != 0) return 0;
+      // the inputs' checks have long come back (what was queued since runs
+      // ahead of the host); on an error the queued work drains into the
+      // workspace only
+      const int r = check_inputs();
+      if (r != 0) {
         (void)hipStreamSynchronize(s);
-        return rc;
+        return r;
       }
       KMP_HIP_TRY(hipMemsetAsync(alpha, 0, sizeof(double) * ncell * n, s));
+      return 0;
+    };
+    const int restart = (spec->flags & KMP_FLAG_RESTART) ? 1 : 0;
+    // The counts of active columns (per group and in total) come back to
+    // pinned memory while the iterations go on: after a poll the next
+    // iteration is queued before the host waits for the counts, so the
+    // device never idles on the round trip (once every column has
+    // converged, that iteration finds nothing to do and the stage ends).
+    const auto post_poll = [&]() -> int {
+      KMP_HIP_TRY(hipMemcpyAsync(poll.p, lay.nact, sizeof(int) * Gb, hipMemcpyDeviceToHost, s));
+      KMP_HIP_TRY(hipMemcpyAsync(poll.p + Gb, lay.active, 2 * sizeof(int), hipMemcpyDeviceToHost, s));
+      KMP_HIP_TRY(hipEventRecord(poll.ev, s));
+      return 0;
+    };
+    const auto read_poll = [&](int* active) -> int {
+      KMP_HIP_TRY(hipEventSynchronize(poll.ev));
+      std::copy(poll.p, poll.p + Gb, nact_h.begin());
+      *active = poll.p[Gb];
+      return 0;
+    };
+    const auto poll_now = [&](int* active) -> int {
+      int r = path_compact(s, pa);
+      if (r == 0) r = post_poll();
+      return r != 0 ? r : read_poll(active);
+    };
+    tm.span(&t_gram, e1, e2);
+    // small orders: every column in one workgroup, from K itself
+    bool small = small_pays(N, spec->loss, nst, (int64_t)Gb * C, C / L) &&
+                 (spec->flags & KMP_FLAG_GLOBAL_SOLVE) == 0;
+    if (small) {
+      SmallStages ss;
+      ss.n = nst;
+      for (int st = 0; st < nst; ++st) {
+        ss.delta[st] = stage_delta(st);
+        ss.kappa[st] = stage_kappa(st);
+      }
+      PathArrays pt = pa;
+      pt.iters = lay.iters_total;
+      int active = Gb * C, most = 0;
+      for (bool begin = true; active > 0; begin = false) {
+        if ((rc = small_path(s, pa, lay.A, ss, spec->tol, spec->max_iter, restart, kSmallChunk,
+                             begin, L)) != 0)
+          return rc;
+        if (begin && (rc = first_checks()) != 0) return rc;
+        if ((rc = path_compact(s, pt)) != 0) return rc;
+        if ((rc = post_poll()) != 0) return rc;
+        if ((rc = read_poll(&active)) != 0) return rc;
+        most = poll.p[Gb + 1];
+        if (most == INT32_MAX) break;
+      }
+      // a column whose f would not settle: this batch in batched form
+      small = most != INT32_MAX;
+      if (small) total_iters += most;
+      else if ((rc = path_init_columns(s, pa)) != 0) return rc;
+      size_t ep = 0;
+      if ((rc = tm.mark(s, &ep)) != 0) return rc;
+      tm.span(&t_path, e2, ep);
+      e2 = ep;
+    }
+    // a2: factorisation
+    if (!small) {
+      BandWork bw = band_work_of(lay, Gb, N, nvg);
+      bw.band_ready = side.band;
+      if ((rc = band_reduce(s, bw)) != 0) return rc;
+      if ((rc = form_qb(s, lay.Qm, lay.band, N, Gb, lay.A)) != 0) return rc;
+      KMP_HIP_TRY(hipStreamWaitEvent(side.st, side.band, 0));
+      side.queued = true;
+      if ((rc = path_stage_factor(side.st, pa, stage_kappa(0))) != 0) return rc;
+      KMP_HIP_TRY(hipEventRecord(side.done, side.st));
+      if ((rc = group_ones_projection(s, lay.Qm, lay.nvg, Gb, N, lay.cvec)) != 0) return rc;
+      if ((rc = tm.mark(s, &e3)) != 0) return rc;
+      tm.span(&t_factor, e2, e3);
+      if ((rc = first_checks()) != 0) return rc;
     }
     // a3-a9: smoothing stages
-    for (int st = 0; st < nst; ++st) {
+    for (int st = 0; st < nst && !small; ++st) {
       const double delta = stage_delta(st);
       const double kappa = stage_kappa(st);
       size_t e4 = 0, e5 = 0, e6 = 0;
@@ -1078,52 +1132,9 @@ int kmp_fit_path(void* stream, const kmp_path_spec* spec, const double* X, int64
       if ((rc = path_stage_vectors(s, pa, kappa)) != 0) return rc;
       if ((rc = path_compact(s, pa)) != 0) return rc;
       if ((rc = tm.mark(s, &e5)) != 0) return rc;
-      // The counts of active columns (per group and in total) come back to
-      // pinned memory while the iterations go on: after a poll the next
-      // iteration is queued before the host waits for the counts, so the
-      // device never idles on the round trip (once every column has
-      // converged, that iteration finds nothing to do and the stage ends).
-      const auto post_poll = [&]() -> int {
-        KMP_HIP_TRY(hipMemcpyAsync(poll.p, lay.nact, sizeof(int) * Gb, hipMemcpyDeviceToHost, s));
-        KMP_HIP_TRY(hipMemcpyAsync(poll.p + Gb, lay.active, 2 * sizeof(int), hipMemcpyDeviceToHost, s));
-        KMP_HIP_TRY(hipEventRecord(poll.ev, s));
-        return 0;
-      };
-      const auto read_poll = [&](int* active) -> int {
-        KMP_HIP_TRY(hipEventSynchronize(poll.ev));
-        std::copy(poll.p, poll.p + Gb, nact_h.begin());
-        *active = poll.p[Gb];
-        return 0;
-      };
-      const int restart = (spec->flags & KMP_FLAG_RESTART) ? 1 : 0;
-      const auto poll_now = [&](int* active) -> int {
-        int r = path_compact(s, pa);
-        if (r == 0) r = post_poll();
-        return r != 0 ? r : read_poll(active);
-      };
       int it = 0;
-      bool dense_on = dense.cap > 0, staged = false;
-      // Orders whose resolvent one compute unit holds: the whole stage in
-      // dense form, cap columns at a time; what a round leaves active (its
-      // launch's iterations used up, or f found drifted) begins again.
-      if (dense_on && N <= kDenseSmall && dense_pays(pa.loss, N, Gb, 0, (int64_t)Gb * C)) {
-        int active = Gb * C;
-        for (int round = 0; active > 0 && round < kDenseChecks + it / kDenseChunk; ++round) {
-          for (int b0 = 0; b0 < active; b0 += dense.cap) {
-            const int cols = std::min(dense.cap, active - b0);
-            if ((rc = dense_begin(s, pa, dense, b0, cols, delta, kappa, spec->tol)) != 0) return rc;
-            if ((rc = dense_iterations(s, pa, dense, cols, delta, kappa, spec->tol, spec->max_iter,
-                                       restart, kDenseChunk)) != 0)
-              return rc;
-            if ((rc = dense_check(s, pa, dense, cols, delta, kappa, spec->tol)) != 0) return rc;
-          }
-          if ((rc = poll_now(&active)) != 0) return rc;
-          it = poll.p[Gb + 1];
-        }
-        dense_on = false;
-        staged = active == 0;
-      }
-      if (!staged) {
+      bool dense_on = dense.cap > 0;
+      {
         IterGraph ig;
         if (use_graphs && (rc = capture_iterations(pa, delta, kappa, spec->tol, spec->max_iter,
                                                    restart, spec->poll_every, &ig)) != 0)
@@ -1133,8 +1144,7 @@ int kmp_fit_path(void* stream, const kmp_path_spec* spec, const double* X, int64
         int dcols = 0, checks = 0;    // columns in dense form (0: the batched iteration)
         while (it < spec->max_iter) {
           if (dcols > 0) {
-            const int count = std::min(N <= kDenseSmall ? kDenseChunk : kDensePoll,
-                                       spec->max_iter - it);
+            const int count = std::min(kDensePoll, spec->max_iter - it);
             if ((rc = dense_iterations(s, pa, dense, dcols, delta, kappa, spec->tol, spec->max_iter,
                                        restart, count)) != 0)
               return rc;
@@ -1171,7 +1181,7 @@ int kmp_fit_path(void* stream, const kmp_path_spec* spec, const double* X, int64
             const int groups = (int)(Gb - std::count(nact_h.begin(), nact_h.end(), 0));
             if (dense_on && dcols == 0 && active <= dense.cap && dense_pays(pa.loss, N, groups, it, active)) {
               if ((rc = path_compact(s, pa)) != 0) return rc;
-              if ((rc = dense_begin(s, pa, dense, 0, active, delta, kappa, spec->tol)) != 0) return rc;
+              if ((rc = dense_begin(s, pa, dense, active, delta, kappa, spec->tol)) != 0) return rc;
               dcols = active;
             }
           }
@@ -1189,8 +1199,6 @@ int kmp_fit_path(void* stream, const kmp_path_spec* spec, const double* X, int64
         if (dcols > 0 &&
             (rc = dense_check(s, pa, dense, dcols, delta, kappa, spec->tol)) != 0)
           return rc;
-        // (a launch of the register form runs no further than its columns)
-        if (dense.cap > 0 && N <= kDenseSmall) it = std::min(it, std::max(1, poll.p[Gb + 1]));
       }
       total_iters += it;
       if ((rc = tm.mark(s, &e6)) != 0) return rc;
@@ -1206,6 +1214,7 @@ int kmp_fit_path(void* stream, const kmp_path_spec* spec, const double* X, int64
     fa.hidx = lay.hidx; fa.Mh = plan.Mh; fa.kh = lay.A; fa.ftrain = lay.fpart;
     fa.alpha = alpha; fa.beta_out = beta; fa.objective = objective; fa.cv_sum = cv_sum;
     fa.shared = shared;
+    fa.direct = small;
     fa.cv_err = cv_err; fa.iters = iters; fa.status = status; fa.stat_count = lay.stat_count;
     if (plan.exact) {
       // the recovery's work vectors reuse column buffers the finalize no

@@ -233,8 +233,8 @@ int path_stage_vectors(hipStream_t s, const PathArrays& p, double kappa);
 int path_iteration(hipStream_t s, const PathArrays& p, double delta, double kappa, double tol,
                    int max_iter, int restart);
 // Rebuilds cmap/nact from the column flags and writes the total number of
-// active columns and the largest of the columns' iteration counts of the
-// stage to active_count (2 ints). The path GEMMs compute only the columns
+// active columns and the largest of the columns' iteration counts (the
+// largest int if a column has flag 4) to active_count (2 ints). The path GEMMs compute only the columns
 // listed in cmap, so it runs after every change of the flags that should
 // shrink the GEMMs (stage start, polls).
 int path_compact(hipStream_t s, const PathArrays& p);
@@ -256,18 +256,36 @@ struct DenseArrays {
 };
 constexpr int kDenseVectors = 9;
 constexpr int kDenseMaxOrder = 3072;
-constexpr int kDenseSmall = 256;    // a column's resolvent fits one compute unit
-// dense_begin takes the active columns first .. first + cols - 1 (cols <=
-// cap) into dense form, dense_iterations runs count iterations of those still
-// active (orders up to kDenseSmall: in one launch). dense_check writes alpha
-// back into ahat, compares f with K alpha and lets a column whose f has
-// drifted go on.
-int dense_begin(hipStream_t s, const PathArrays& p, const DenseArrays& a, int first, int cols,
-                double delta, double kappa, double tol);
+// dense_begin takes the active columns (at most cols of them, cols <= cap) into
+// dense form, dense_iterations runs count iterations of those still active.
+// dense_check writes alpha back into ahat, compares f with K alpha and lets a
+// column whose f has drifted go on.
+int dense_begin(hipStream_t s, const PathArrays& p, const DenseArrays& a, int cols, double delta,
+                double kappa, double tol);
 int dense_iterations(hipStream_t s, const PathArrays& p, const DenseArrays& a, int cols, double delta,
                      double kappa, double tol, int max_iter, int restart, int count);
 int dense_check(hipStream_t s, const PathArrays& p, const DenseArrays& a, int cols, double delta,
                 double kappa, double tol);
+// Small orders (small.hip): every column through all smoothing stages in one
+// launch, at most count iterations of it, from K (G x N x N) without a
+// factorisation; ahat and abar hold alpha and its extrapolation in observation
+// space. begin: the first launch (flags 0, ahat 0). Columns that count stops
+// stay active for a further launch; flag 4 marks one whose f keeps drifting.
+constexpr int kSmallOrder = 256, kSmallStages = 8;
+struct SmallStages {
+  int n = 0;
+  double delta[kSmallStages], kappa[kSmallStages];
+};
+// Whether a fit of `cols` columns, `same` of them with one group and penalty,
+// goes this way. The hinge and check losses take hundreds of iterations a
+// column and always gain (5000 leave-one-out columns of 250 rows: 189 ms with
+// the factorisation, 91 without). The logistic loss takes tens, so the sweeps
+// decide where each compute unit forms many resolvents: five folds of 310 rows
+// (order 256) take 2.08 ms (2.62 batched) at 2 each, 3.73 (2.93) at 4, of 230
+// rows (order 192) 3.98 (4.75) at 16, growing by 0.23 (0.17) each.
+bool small_pays(int N, int loss, int stages, int64_t cols, int64_t same);
+int small_path(hipStream_t s, const PathArrays& p, const double* K, const SmallStages& st, double tol,
+               int max_iter, int restart, int count, bool begin, int L);
 // R = Q Y' for the nblk blocks of 64 rows of Y from block e0 (dgemm.hip).
 int resolvent_gemm(hipStream_t s, int N, int C, int e0, int nblk, const double* Q,
                    const DenseArrays& a);
@@ -332,6 +350,7 @@ struct FinalArgs {
   int* stat_count = nullptr;       // 3 ints, accumulated: cells at max_iter, non-finite
                                    // cells, cells whose exact hinge solution was not reached
   bool shared = false;             // shared-factor mode (one group per bandwidth, all n rows)
+  bool direct = false;             // ahat holds alpha itself and kh K_v (small.hip)
   bool exact = false;              // recover the exact hinge SVM (objective: eq. (kernelsvm))
   ExactArgs ex;                    // its buffers (ex.cols > 0 when exact)
   int exact_rounds = 128;          // active-set rounds at most

@@ -1694,7 +1694,8 @@ __global__ __launch_bounds__(PB) void compact_columns_kernel(int G, int C,
     for (int c0 = 0; c0 < C; c0 += 64) {
       const int c = c0 + lane;
       const bool act = c < C && flag[(int64_t)g * C + c] == 0;
-      if (c < C) mi = max(mi, iters[(int64_t)g * C + c]);
+      if (c < C)
+        mi = max(mi, flag[(int64_t)g * C + c] == 4 ? 0x7fffffff : iters[(int64_t)g * C + c]);
       const unsigned long long m = __ballot(act);
       const int rank = __popcll(m & ((1ull << lane) - 1ull));
       if (act) cmap[(int64_t)g * C + base + rank] = c;
@@ -1931,11 +1932,15 @@ static int path_finalize_shared(hipStream_t s, const PathArrays& p, const FinalA
   g.A = p.Q; g.lda = p.N; g.sA = (int64_t)p.N * p.N;
   g.B = p.ahat; g.ldb = p.N; g.sB = sNC;
   g.C = p.zmat; g.ldc = p.N; g.sC = sNC;
-  if ((rc = gemm_split(s, g, p.fpart, sP)) != 0) return rc;
+  if (fa.direct)
+    KMP_HIP_TRY(hipMemcpyAsync(p.zmat, p.ahat, sizeof(double) * (size_t)sP, hipMemcpyDeviceToDevice, s));
+  else if ((rc = gemm_split(s, g, p.fpart, sP)) != 0)
+    return rc;
   hipLaunchKernelGGL(mask_heldout_kernel, dim3((unsigned)ceil_div(p.N, 256), (unsigned)cols),
                      dim3(256), 0, s, p.N, p.C, p.rfold, p.cfold, p.zmat);
   KMP_LAUNCH_CHECK();
-  if ((rc = rbf_blocks(s, fa.X, fa.d, fa.ldx, fa.tidx, p.N, p.N, fa.tidx, p.N, p.N, 1,
+  if (!fa.direct &&
+      (rc = rbf_blocks(s, fa.X, fa.d, fa.ldx, fa.tidx, p.N, p.N, fa.tidx, p.N, p.N, 1,
                        fa.inv2s2, fa.S_b, fa.kh, (int64_t)p.N * p.N, (int64_t)p.N * p.N, p.N)) != 0)
     return rc;
   GemmArgs gt = g;
@@ -1970,11 +1975,15 @@ int path_finalize(hipStream_t s, const PathArrays& p, const FinalArgs& fa) {
   g.C = p.zmat; g.ldc = p.N; g.sC = sNC;
   // (the parts of this product go to fpart, those of the next to zpart:
   // the training predictions are stored in fpart)
-  if ((rc = gemm_split(s, g, p.fpart, sP)) != 0) return rc;
+  if (fa.direct)
+    KMP_HIP_TRY(hipMemcpyAsync(p.zmat, p.ahat, sizeof(double) * (size_t)sP, hipMemcpyDeviceToDevice, s));
+  else if ((rc = gemm_split(s, g, p.fpart, sP)) != 0)
+    return rc;
   // training predictions K_v alpha in observation space: K_v is built again
   // from X into the factor buffer (no longer needed) and multiplied by
   // alpha, so the objective does not carry the factorisation's rounding
-  if ((rc = rbf_blocks(s, fa.X, fa.d, fa.ldx, fa.tidx, p.N, p.N, fa.tidx, p.N, p.N,
+  if (!fa.direct &&
+      (rc = rbf_blocks(s, fa.X, fa.d, fa.ldx, fa.tidx, p.N, p.N, fa.tidx, p.N, p.N,
                        fa.V, fa.inv2s2, fa.S_b, fa.kh, (int64_t)fa.V * p.N * p.N,
                        (int64_t)p.N * p.N, p.N)) != 0)
     return rc;

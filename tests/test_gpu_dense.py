@@ -1,8 +1,9 @@
-"""The dense form of a stage's last columns (dense.hip) against the batched
-iteration (KMP_FLAG_GLOBAL_SOLVE, which never takes it) on the same problem:
-the objective and coefficient bars of the oracle comparisons. Sizes lie on the
-edges of its variants: orders 64 to 256 (one compute unit per column), the
-first order above, odd sizes, and more columns than one area holds."""
+"""Small orders (small.hip: a column's whole path in one workgroup) and the
+dense form of a stage's last columns (dense.hip) against the batched iteration
+(KMP_FLAG_GLOBAL_SOLVE, which takes neither) on the same problem: the objective
+and coefficient bars of the oracle comparisons. Sizes lie on the edges of the
+variants: orders 64 to 256, the first order above, odd sizes, and more columns
+than compute units."""
 import numpy as np
 import pytest
 
@@ -56,31 +57,40 @@ def test_dense_matches_batched(loss, n, V, mode):
     _agree(a, b)
 
 
-def test_dense_more_columns_than_the_area_holds():
-    """n = 190 leave-one-out: 190 x 6 columns of order 192 against 900 in the
-    area; the batched iteration first, then two areas' worth."""
+def test_small_leave_one_out():
+    """n = 190: 1140 columns of order 192, several per compute unit."""
     inp = W.small_problem("hinge", 190, 4, seed=7, V=2, L=6, lam_lo=-3.0, lam_hi=0.0)
     inp["fold_id"], inp["V"] = np.arange(190, dtype=np.int32), 190
-    announce("dense columns, leave-one-out n=190 L=6")
+    announce("small order, leave-one-out n=190 L=6")
     _agree(*_both(inp, "hinge", shared=True))
+
+
+@pytest.mark.parametrize("n,L", [(67, 8), (130, 7), (150, 3)])
+def test_small_one_resolvent_for_several_columns(n, L):
+    """Logistic leave-one-out: the columns of a penalty share the resolvent, in
+    runs that end inside a penalty's columns and inside the last workgroup's."""
+    inp = W.small_problem("logistic", n, 4, seed=n, V=2, L=L, lam_lo=-3.0, lam_hi=0.0)
+    inp["fold_id"], inp["V"] = np.arange(n, dtype=np.int32), n
+    announce(f"small order, logistic leave-one-out n={n} L={L}")
+    _agree(*_both(inp, "logistic", shared=True))
 
 
 def test_dense_needs_no_workspace():
     """A workspace without the optional part runs batched iterations only, one
     with part of it takes fewer columns: the same results to rounding."""
-    inp = W.small_problem("hinge", 150, 4, seed=8, V=3, L=5, lam_lo=-3.0, lam_hi=0.0)
+    inp = W.small_problem("hinge", 450, 4, seed=8, V=3, L=5, lam_lo=-3.0, lam_hi=0.0)
     sizes = []
 
     def fixed(extra):
         def size(r, km):
             spec = km.kmp_default_spec("hinge", flags=r.spec.flags | km.KMP_FLAG_GLOBAL_SOLVE)
-            b = km.kmp_workspace_bytes(spec, 150, 4, 5, r.fold, 3, 1, 1, 1)
+            b = km.kmp_workspace_bytes(spec, 450, 4, 5, r.fold, 3, 1, 1, 1)
             sizes.append((b, r.ws_bytes))
             return b + extra
         return size
 
     announce("dense columns: workspace without the optional part")
-    for extra in (0, 400_000):
+    for extra in (0, 72 << 20):
         _agree(*_both(inp, "hinge", ws=fixed(extra)))
     assert sizes[0][0] < sizes[0][1]
 

@@ -285,8 +285,9 @@ int kmp_band_reduce(void* stream, double* A, int32_t G, int32_t N, double* Qout,
  * caller-given state, for C columns of one problem (Appendix A.1, the update
  * (beta, alpha) <- (beta, alpha) - H^{-1} (1'z ; K z + 2 lambda K alpha),
  * z_i = psi(y_i, f_i)/n, f = K alpha + beta; H applied through the block
- * form of its inverse of Appendix A.3, here in the band basis of K's
- * factorisation K = Q B Q'). Column c has penalty lambdas[c] (and level
+ * form of its inverse of Appendix A.3, with a Cholesky factor of 2 lambda I +
+ * K/(n kappa) per column where that is the less work (n <= 4096) and every
+ * pivot is positive, else in the band basis of K = Q B Q'). Column c has penalty lambdas[c] (and level
  * taus[c] for KMP_CHECK); the curvature bound is 1/kappa with kappa = 2 delta
  * (hinge, check) or 4 (logistic, delta ignored). No extrapolation: the step
  * is taken from the given point itself.

@@ -891,6 +891,116 @@ int resolvent_gemm(hipStream_t s, int N, int C, int e0, int nblk, const double* 
   return 0;
 }
 
+// Panel J of the columns' Cholesky factors (left-looking; StepArrays). Each
+// workgroup takes a 64 x 64 tile (I, J), I = J .. N/64 (the last one the
+// right-hand sides): T = M_IJ - sum_{k < 64 J} G_Ik G_Jk', with M formed from
+// K here, so K is read once and no tile of the factor more than once a panel.
+// The workgroup of the diagonal tile, the launch's chain and started first,
+// goes on to factor it: lane i of wavefront w holds columns 16 w .. 16 w + 15 of
+// row i of T and of the identity, 64 elimination steps turn them into D L' and
+// L^{-1}, and D^{-1/2} L^{-1} is kept. One barrier a step (the column through
+// LDS, the row by readlane).
+__global__ __launch_bounds__(256) void step_panel_kernel(const StepArrays a, int c0, int J) {
+  __shared__ double colb[2][64];
+  const int I = J + (int)blockIdx.x, N = a.N, n = a.n, b = blockIdx.y, c = c0 + b;
+  double* P = a.P + (int64_t)b * (N + 64) * N;
+  dbl4 acc[2][2];
+  tile_mainloop_vec<64, 16, true>(64, 0, 64 * J, 64 * I, 0, P, N, P + (int64_t)64 * J * N, N, nullptr,
+                                  acc);
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wi = (w & 1) * 32, wj = (w >> 1) * 32;
+  const double sc = 1.0 / ((double)n * a.kappa), lam2 = 2.0 * a.lam[c];
+#pragma unroll
+  for (int bi = 0; bi < 2; ++bi)
+#pragma unroll
+    for (int bj = 0; bj < 2; ++bj)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int i = 64 * I + wi + bi * 16 + mfma_row(lane, r);
+        const int j = 64 * J + wj + bj * 16 + mfma_col(lane);
+        double m = 0.0;
+        if (i >= N) {
+          if (j < n && i == N) m = a.w[(int64_t)c * N + j];
+          if (j < n && i == N + 1) m = sc;
+        } else {
+          if (i < n && j < n) m = sc * a.K[(int64_t)i * n + j];
+          if (i == j) m += lam2;
+        }
+        P[(int64_t)i * N + j] = m - acc[bi][bj][r];
+      }
+  if (I != J) return;                             // uniform over the block
+  __syncthreads();
+  double T[16], W[16], mine = 1.0;
+  const double* row = P + (int64_t)(64 * J + lane) * N + 64 * J + 16 * w;
+#pragma unroll
+  for (int q = 0; q < 16; ++q) {
+    T[q] = row[q];
+    W[q] = lane == 16 * w + q ? 1.0 : 0.0;
+  }
+  const auto from = [](double v, int l) {         // v of lane l
+    const long long u = __double_as_longlong(v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)u, l);
+    const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(u >> 32), l);
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+  };
+#pragma unroll 1
+  for (int kq = 0; kq < 4; ++kq) {
+#pragma unroll
+    for (int kk = 0; kk < 16; ++kk) {
+      const int k = 16 * kq + kk;
+      if (w == kq) colb[kk & 1][lane] = T[kk];
+      __syncthreads();
+      const double d = colb[kk & 1][k];
+      if (lane == k) mine = d;
+      const double l = lane > k ? colb[kk & 1][lane] * rcp_newton(d) : 0.0;
+#pragma unroll
+      for (int q = 0; q < 16; ++q) {
+        T[q] = fma(-l, from(T[q], k), T[q]);
+        W[q] = fma(-l, from(W[q], k), W[q]);
+      }
+    }
+  }
+  // (a NaN pivot counts as not positive)
+  const bool ok = mine > 0.0 && mine < 1e300;
+  if (!ok) *a.bad = 1;
+  const double g = ok ? 1.0 / sqrt(mine) : 0.0;
+  double* out = a.dinv + ((int64_t)b * N + 64 * J + lane) * 64 + 16 * w;
+#pragma unroll
+  for (int q = 0; q < 16; ++q) out[q] = W[q] * g;
+}
+
+// G_IJ = T_IJ G_JJ^{-T} for I > J, in place (a tile is read whole before it
+// is written).
+__global__ __launch_bounds__(256) void step_trsm_kernel(const StepArrays a, int J) {
+  const int I = J + 1 + (int)blockIdx.x, N = a.N, b = blockIdx.y;
+  double* P = a.P + (int64_t)b * (N + 64) * N;
+  dbl4 acc[2][2];
+  tile_mainloop_vec<64, 16, true>(64, 0, 64, 64 * I, 0, P + 64 * J, N,
+                                  a.dinv + ((int64_t)b * N + 64 * J) * 64, 64, nullptr, acc);
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int wi = (w & 1) * 32, wj = (w >> 1) * 32;
+#pragma unroll
+  for (int bi = 0; bi < 2; ++bi)
+#pragma unroll
+    for (int bj = 0; bj < 2; ++bj)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int i = 64 * I + wi + bi * 16 + mfma_row(lane, r);
+        const int j = 64 * J + wj + bj * 16 + mfma_col(lane);
+        P[(int64_t)i * N + j] = acc[bi][bj][r];
+      }
+}
+
+int step_panel(hipStream_t s, const StepArrays& a, int c0, int cols, int J) {
+  const int nb = a.N / 64;
+  hipLaunchKernelGGL(step_panel_kernel, dim3((unsigned)(nb + 1 - J), (unsigned)cols), dim3(256), 0, s,
+                     a, c0, J);
+  KMP_LAUNCH_CHECK();
+  hipLaunchKernelGGL(step_trsm_kernel, dim3((unsigned)(nb - J), (unsigned)cols), dim3(256), 0, s, a, J);
+  KMP_LAUNCH_CHECK();
+  return 0;
+}
+
 int loss_epilogue(hipStream_t s, int M, int N, int batch, int S, const double* part, int64_t ldc,
                   int64_t sC, int64_t sP, double* Z, const LossEpi& e, const int* cmap,
                   const int* nact) {

@@ -1379,6 +1379,8 @@ int kmp_dgemm_grouped(void* stream, int32_t G, int32_t M, int32_t N, int32_t K, 
   return KMP_OK;
 }
 
+constexpr size_t kStepBytes = (size_t)2 << 30;
+
 int kmp_path_step(void* stream, int32_t loss, double delta, const double* K, int64_t n,
                   const double* y, const double* lambdas, const double* taus, int32_t C,
                   const double* alpha_in, const double* beta_in, double* alpha_out,
@@ -1411,6 +1413,43 @@ int kmp_path_step(void* stream, int32_t loss, double delta, const double* K, int
   if (n > kMaxOrder) {
     set_error("kmp_path_step: n above the largest factor order");
     return KMP_EINVAL;
+  }
+  const auto direct = [&](bool* done) -> int {
+    // columns factored at once: at most kStepBytes of factors
+    StepArrays a;
+    a.n = (int)n; a.N = plan.N; a.C = C; a.loss = loss;
+    a.kappa = loss == KMP_LOGISTIC ? 4.0 : 2.0 * delta;
+    a.delta = loss == KMP_LOGISTIC ? 1.0 : delta;
+    a.K = K; a.y = y; a.alpha_in = alpha_in; a.beta_in = beta_in;
+    const size_t per = sizeof(double) * ((size_t)plan.N + 128) * plan.N;
+    a.cap = (int)std::max<size_t>(1, std::min<size_t>(C, kStepBytes / per));
+    void* ws = nullptr;
+    if (hipMallocAsync(&ws, sizeof(double) * step_doubles(plan.N, C, a.cap), s) != hipSuccess) {
+      (void)hipGetLastError();
+      return 0;                        // too little memory left: by the factorisation of K
+    }
+    step_carve(&a, static_cast<double*>(ws));
+    std::vector<double> lam(lambdas, lambdas + C), tau(C, 0.0);
+    if (loss == KMP_CHECK) tau.assign(taus, taus + C);
+    int bad = 1;
+    const auto queue = [&]() -> int {
+      KMP_HIP_TRY(hipMemcpyAsync((void*)a.lam, lam.data(), sizeof(double) * C, hipMemcpyHostToDevice, s));
+      KMP_HIP_TRY(hipMemcpyAsync((void*)a.tau, tau.data(), sizeof(double) * C, hipMemcpyHostToDevice, s));
+      const int r = step_columns(s, a, alpha_out, beta_out, kkt_out);
+      if (r != 0) return r;
+      KMP_HIP_TRY(hipMemcpyAsync(&bad, a.bad, sizeof(int), hipMemcpyDeviceToHost, s));
+      return 0;
+    };
+    const int r = queue();
+    (void)hipFreeAsync(ws, s);
+    KMP_HIP_TRY(hipStreamSynchronize(s));
+    *done = bad == 0;
+    return r;
+  };
+  if (step_pays(n, C)) {
+    bool done = false;
+    if ((rc = direct(&done)) != 0) return rc;
+    if (done) return KMP_OK;           // else some pivot was not positive: nothing written
   }
   // make_plan lays out C = Q L columns with Q = 1, L = C
   const int N = plan.N;

@@ -286,6 +286,34 @@ struct SmallStages {
 bool small_pays(int N, int loss, int stages, int64_t cols, int64_t same);
 int small_path(hipStream_t s, const PathArrays& p, const double* K, const SmallStages& st, double tol,
                int max_iter, int restart, int count, bool begin, int L);
+// One step of the path on a caller's K by a Cholesky factor per column
+// (step.hip, its tiles in dgemm.hip). Rows padded to N = 64 nb; column c's
+// factor G of M = 2 lambda I + K/(n kappa) is kept as N x N row-major lower
+// tiles (those on the diagonal only by the inverses in dinv), followed by a
+// 64-row tile whose first two rows are the right-hand sides, (w, 1/(n kappa))
+// before the factorisation and (G^{-1} of them)' after it.
+struct StepArrays {
+  int n = 0, N = 0, C = 0, loss = 0, cap = 0;   // cap: columns factored at once
+  double kappa = 1.0, delta = 1.0;
+  const double *K = nullptr, *y = nullptr, *alpha_in = nullptr, *beta_in = nullptr;
+  const double *lam = nullptr, *tau = nullptr;
+  double *f = nullptr, *kv = nullptr;           // C x n: K alpha, then K x; K v
+  double *w = nullptr, *x = nullptr, *v = nullptr, *r0 = nullptr, *r1 = nullptr;   // C x N
+  double* kkt = nullptr;                        // C
+  double *P = nullptr;                          // cap x (N + 64) x N
+  double *dinv = nullptr;                       // cap x N x 64
+  int* bad = nullptr;                           // a pivot was not positive
+};
+// Device doubles of the arrays above besides the caller's, for `cap` columns.
+size_t step_doubles(int N, int C, int cap);
+void step_carve(StepArrays* a, double* base);
+constexpr int kStepMaxOrder = 4096;
+// Whether n, C go this way.
+bool step_pays(int64_t n, int C);
+int step_columns(hipStream_t s, const StepArrays& a, double* alpha_out, double* beta_out,
+                 double* kkt_out);
+// Panel J of columns c0 .. c0 + cols - 1 (dgemm.hip).
+int step_panel(hipStream_t s, const StepArrays& a, int c0, int cols, int J);
 // R = Q Y' for the nblk blocks of 64 rows of Y from block e0 (dgemm.hip).
 int resolvent_gemm(hipStream_t s, int N, int C, int e0, int nblk, const double* Q,
                    const DenseArrays& a);

@@ -1,0 +1,74 @@
+"""kmp_path_step by a Cholesky factor per column (step.hip) against the
+oracle's dense step: orders on the edges of its 64-row tiles, one and several
+columns, odd leading dimensions, in place, and matrices whose 2 lambda I +
+K/(n kappa) is not positive definite, which go by the factorisation of K."""
+import numpy as np
+import pytest
+
+from oracle import gram as OG
+from oracle import losses as OL
+from tests.gpu_common import announce, device
+
+pytestmark = pytest.mark.gpu
+
+STEP_RTOL = 1e-9     # that of the single-step test: relative to the larger max |alpha|
+
+
+def _mm_step(K, y, alpha, beta, lam, loss, delta, tau, kap):
+    """oracle.mm.mm_step with a pivoted solve, for M of either sign."""
+    n = y.shape[0]
+    z = OL.point_psi(loss, y, K @ alpha + beta, delta, tau) / n
+    w, d0 = z + 2.0 * lam * alpha, z.sum()
+    M = 2.0 * lam * np.eye(n) + K / (n * kap)
+    x, v = np.linalg.solve(M, np.stack([w, np.full(n, 1.0 / (n * kap))], axis=1)).T
+    g, t = 1.0 / (2.0 * lam * v.sum()), v @ (K @ w)
+    return alpha - x - g * (t - d0) * v, beta - g * (d0 - t)
+
+
+def _step(loss, n, C, K, in_place=False, lam_lo=-4.0):
+    import torch
+    from paper_2606_06742_amd import kmpath as km
+    dev = device()
+    rng = np.random.default_rng(n + C)
+    y = np.where(rng.standard_normal(n) > 0, 1.0, -1.0) if loss != "check" else rng.standard_normal(n)
+    lambdas = 10.0 ** np.linspace(lam_lo, 0.0, C)
+    delta = None if loss == "logistic" else 0.125
+    taus = np.linspace(0.1, 0.9, C) if loss == "check" else None
+    A = rng.uniform(-1, 1, (C, n)) / (2 * n * lambdas[:, None])
+    B = rng.uniform(-0.5, 0.5, C)
+    t = lambda a: torch.as_tensor(np.ascontiguousarray(a), dtype=torch.float64, device=dev)
+    a_in, b_in = t(A), t(B)
+    a_out, b_out = (a_in, b_in) if in_place else (torch.empty_like(a_in), torch.empty_like(b_in))
+    kkt = torch.empty_like(b_in)
+    announce(f"kmp_path_step loss={loss} n={n} C={C} in_place={in_place}")
+    km.kmp_path_step(loss, delta, t(K), t(y), lambdas, a_in, b_in, a_out, b_out, kkt, taus=taus)
+    torch.cuda.synchronize()
+    ag, bg, kg = a_out.cpu().numpy(), b_out.cpu().numpy(), kkt.cpu().numpy()
+    kap = OL.kappa(loss, delta)
+    for c in range(C):
+        tau = taus[c] if taus is not None else None
+        ao, bo = _mm_step(K, y, A[c], B[c], lambdas[c], loss, delta, tau, kap)
+        scale = max(np.abs(ao).max(), np.abs(A[c]).max())
+        assert np.abs(ag[c] - ao).max() <= STEP_RTOL * scale, c
+        assert abs(bg[c] - bo) <= STEP_RTOL * max(1.0, abs(bo), np.abs(A[c]).max()), c
+        z = OL.point_psi(loss, y, K @ A[c] + B[c], delta, tau) / n
+        ko = n * max(np.linalg.norm(z + 2 * lambdas[c] * A[c]), abs(z.sum()))
+        assert abs(kg[c] - ko) <= 1e-9 * ko, c
+
+
+@pytest.mark.parametrize("loss,n,C", [
+    ("hinge", 2, 1), ("check", 63, 3), ("logistic", 64, 5), ("hinge", 65, 1), ("check", 128, 17),
+    ("logistic", 191, 2), ("hinge", 449, 33),
+])
+def test_step_edges(loss, n, C):
+    X = np.random.default_rng(n).standard_normal((n, 3))
+    _step(loss, n, C, OG.rbf_gram(X, X, 1.5), in_place=n % 2 == 1)
+
+
+def test_step_without_positive_pivots():
+    """Eigenvalues of K far below zero: the dense step still exists, and the call
+    gives it as before."""
+    n = 100
+    U, _ = np.linalg.qr(np.random.default_rng(1).standard_normal((n, n)))
+    e = np.linspace(-40.0, 60.0, n)
+    _step("hinge", n, 2, (U * e) @ U.T, lam_lo=-1.0)

@@ -899,7 +899,9 @@ int resolvent_gemm(hipStream_t s, int N, int C, int e0, int nblk, const double* 
 // goes on to factor it: lane i of wavefront w holds columns 16 w .. 16 w + 15 of
 // row i of T and of the identity, 64 elimination steps turn them into D L' and
 // L^{-1}, and D^{-1/2} L^{-1} is kept. One barrier a step (the column through
-// LDS, the row by readlane).
+// LDS, the row by readlane). At N = 1408 and 20 columns a launch takes 38 us for
+// the first panel, all elimination, to 92 us for the last, whose products run
+// over 1344 rows; the solves of the tiles below 8 us.
 __global__ __launch_bounds__(256) void step_panel_kernel(const StepArrays a, int c0, int J) {
   __shared__ double colb[2][64];
   const int I = J + (int)blockIdx.x, N = a.N, n = a.n, b = blockIdx.y, c = c0 + b;

@@ -299,7 +299,7 @@ struct StepArrays {
   const double *lam = nullptr, *tau = nullptr;
   double *f = nullptr, *kv = nullptr;           // C x n: K alpha, then K x; K v
   double *w = nullptr, *x = nullptr, *v = nullptr, *r0 = nullptr, *r1 = nullptr;   // C x N
-  double* kkt = nullptr;                        // C
+  double *kkt = nullptr, *stay = nullptr;       // C
   double *P = nullptr;                          // cap x (N + 64) x N
   double *dinv = nullptr;                       // cap x N x 64
   int* bad = nullptr;                           // a pivot was not positive

@@ -86,7 +86,12 @@ __global__ __launch_bounds__(ST) void step_loss_kernel(const StepArrays a) {
   }
   zs = block_sum<ST / 64>(zs, red[0]);
   n2 = block_sum<ST / 64>(n2, red[1]);
-  if (threadIdx.x == 0) a.kkt[c] = (double)n * fmax(sqrt(n2), fabs(zs));
+  if (threadIdx.x == 0) {
+    // (fmax drops a NaN, so both terms are tested)
+    const double kkt = (double)n * fmax(sqrt(n2), fabs(zs));
+    a.kkt[c] = kkt;
+    a.stay[c] = !(n2 == n2) || !(zs == zs) || !(kkt <= 1e300) ? 1.0 : 0.0;
+  }
 }
 
 // The two solutions of a column from its factor, a workgroup per column. The
@@ -214,9 +219,10 @@ __global__ __launch_bounds__(ST) void step_finish_kernel(const StepArrays a, dou
   }
   vs = block_sum<ST / 64>(vs, red[0]);
   t = block_sum<ST / 64>(t, red[1]);
-  const double q = t / vs;
+  const bool stay = a.stay[c] != 0.0;             // no step from a state that is not finite
+  const double q = stay ? 0.0 : t / vs;
   for (int i = threadIdx.x; i < n; i += ST)
-    alpha_out[(int64_t)c * n + i] = fma(-q, v[i], al[i] - x[i]);
+    alpha_out[(int64_t)c * n + i] = stay ? al[i] : fma(-q, v[i], al[i] - x[i]);
   if (threadIdx.x == 0) {
     beta_out[c] = a.beta_in[c] + q;
     if (kkt_out) kkt_out[c] = a.kkt[c];
@@ -236,7 +242,7 @@ bool step_pays(int64_t n, int C) {
 
 size_t step_doubles(int N, int C, int cap) {
   const size_t n = (size_t)N, c = (size_t)C, k = (size_t)cap;
-  return 7 * c * n + 3 * c + k * ((n + 64) * n + 64 * n) + 2;
+  return 7 * c * n + 4 * c + k * ((n + 64) * n + 64 * n) + 2;
 }
 
 void step_carve(StepArrays* a, double* q) {
@@ -251,6 +257,7 @@ void step_carve(StepArrays* a, double* q) {
   a->r0 = q; q += c * n;
   a->r1 = q; q += c * n;
   a->kkt = q; q += c;
+  a->stay = q; q += c;
   a->lam = q; q += c;
   a->tau = q; q += c;
   a->bad = reinterpret_cast<int*>(q);

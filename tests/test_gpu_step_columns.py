@@ -72,3 +72,26 @@ def test_step_without_positive_pivots():
     U, _ = np.linalg.qr(np.random.default_rng(1).standard_normal((n, n)))
     e = np.linspace(-40.0, 60.0, n)
     _step("hinge", n, 2, (U * e) @ U.T, lam_lo=-1.0)
+
+
+def test_step_from_a_state_that_is_not_finite():
+    """A column whose state is not finite keeps it, and the others step."""
+    import torch
+    from paper_2606_06742_amd import kmpath as km
+    dev = device()
+    n = 70
+    rng = np.random.default_rng(5)
+    X = rng.standard_normal((n, 3))
+    t = lambda a: torch.as_tensor(np.ascontiguousarray(a), dtype=torch.float64, device=dev)
+    a_in, y = t(rng.uniform(-1, 1, (3, n)) / n), t(np.where(X[:, 0] > 0, 1.0, -1.0))
+    announce("kmp_path_step: an intercept that is not a number")
+    out = []
+    for beta in (0.1, np.nan):
+        b_in = t([0.2, beta, 0.3])
+        a, b, k = torch.empty_like(a_in), torch.empty_like(b_in), torch.empty_like(b_in)
+        km.kmp_path_step("logistic", None, t(OG.rbf_gram(X, X, 1.5)), y, np.array([0.1, 0.01, 1.0]),
+                         a_in, b_in, a, b, k)
+        out.append((a.cpu().numpy(), b.cpu().numpy()))
+    (a0, b0), (a1, b1) = out
+    assert np.array_equal(a0[[0, 2]], a1[[0, 2]]) and np.array_equal(b0[[0, 2]], b1[[0, 2]])
+    assert np.array_equal(a1[1], a_in[1].cpu().numpy()) and np.isnan(b1[1])

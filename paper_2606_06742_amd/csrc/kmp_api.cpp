@@ -896,6 +896,7 @@ int kmp_fit_path(void* stream, const kmp_path_spec* spec, const double* X, int64
     return spec->loss == KMP_LOGISTIC ? 4.0 : 2.0 * stage_delta(st);
   };
   const double delta_final = stage_delta(nst - 1);
+  const double lam_least = *std::min_element(lambdas, lambdas + L);
 
   // host-side index lists and per-column parameters
   // row lists: the training points of each fold, or (shared factor) every
@@ -1072,7 +1073,7 @@ int kmp_fit_path(void* stream, const kmp_path_spec* spec, const double* X, int64
     };
     tm.span(&t_gram, e1, e2);
     // small orders: every column in one workgroup, from K itself
-    bool small = small_pays(N, spec->loss, nst, (int64_t)Gb * C, C / L) &&
+    bool small = small_pays(N, spec->loss, nst, (int64_t)Gb * C, C / L, 2.0 * lam_least * stage_kappa(nst - 1)) &&
                  (spec->flags & KMP_FLAG_GLOBAL_SOLVE) == 0;
     if (small) {
       SmallStages ss;
@@ -1095,7 +1096,7 @@ int kmp_fit_path(void* stream, const kmp_path_spec* spec, const double* X, int64
         most = poll.p[Gb + 1];
         if (most == INT32_MAX) break;
       }
-      // a column whose f would not settle: this batch in batched form
+      // a column whose f would not settle on K alpha: this batch in batched form
       small = most != INT32_MAX;
       if (small) total_iters += most;
       else if ((rc = path_init_columns(s, pa)) != 0) return rc;

@@ -214,7 +214,9 @@ struct PathArrays {
   double* rmom = nullptr;
   double* gcoef = nullptr;
   double* kkt = nullptr;
-  int* flag = nullptr;      // 0 active, 1 converged, 2 max_iter, 3 non-finite
+  // 0 active, 1 converged, 2 max_iter, 3 non-finite, 4 (small_path only) left to
+  // the batched iteration
+  int* flag = nullptr;
   int* iters = nullptr;     // per stage
   int* iters_total = nullptr;
   int* active_count = nullptr;  // 2 ints
@@ -270,20 +272,27 @@ int dense_check(hipStream_t s, const PathArrays& p, const DenseArrays& a, int co
 // launch, at most count iterations of it, from K (G x N x N) without a
 // factorisation; ahat and abar hold alpha and its extrapolation in observation
 // space. begin: the first launch (flags 0, ahat 0). Columns that count stops
-// stay active for a further launch; flag 4 marks one whose f keeps drifting.
+// stay active for a further launch; flag 4 marks one whose carried f would not
+// settle on K alpha or is not finite.
 constexpr int kSmallOrder = 256, kSmallStages = 8;
 struct SmallStages {
   int n = 0;
   double delta[kSmallStages], kappa[kSmallStages];
 };
-// Whether a fit of `cols` columns, `same` of them with one group and penalty,
-// goes this way. The hinge and check losses take hundreds of iterations a
+// The least 2 lambda kappa, the shift of K/n_v in a resolvent's matrix, with which
+// an explicit resolvent and the recurrence for f are used: the errors of both are
+// its inverse times the rounding. Below (the smallest penalties of a fit at its
+// last smoothing level) the steps themselves are too far off: at 1e-11 a column
+// of 180 rows stayed at a residual of 90 where the batched iteration came to 5e-3.
+constexpr double kLeastShift = 1e-9;
+// Whether a fit of `cols` columns, `same` of them with one group and penalty and
+// `least` the least 2 lambda kappa of any, goes this way. The hinge and check losses take hundreds of iterations a
 // column and always gain (5000 leave-one-out columns of 250 rows: 189 ms with
 // the factorisation, 91 without). The logistic loss takes tens, so the sweeps
 // decide where each compute unit forms many resolvents: five folds of 310 rows
 // (order 256) take 2.08 ms (2.62 batched) at 2 each, 3.73 (2.93) at 4, of 230
 // rows (order 192) 3.98 (4.75) at 16, growing by 0.23 (0.17) each.
-bool small_pays(int N, int loss, int stages, int64_t cols, int64_t same);
+bool small_pays(int N, int loss, int stages, int64_t cols, int64_t same, double least);
 int small_path(hipStream_t s, const PathArrays& p, const double* K, const SmallStages& st, double tol,
                int max_iter, int restart, int count, bool begin, int L);
 // One step of the path on a caller's K by a Cholesky factor per column

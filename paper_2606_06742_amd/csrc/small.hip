@@ -18,7 +18,10 @@
 // Five folds of 200 rows by ten penalties, hinge loss: 69.5 ms in batched
 // form, 5.2 with the resolvents formed from the factorisation and a launch per
 // stage, 4.0 here; leave-one-out, 151 rows, logistic loss: 3.2, 2.9, 0.90 ms.
-// f is compared with K alpha (K read again) before a column may stop.
+// f is carried by the recurrence, whose rounding grows as lambda shrinks (n = 180,
+// lambda = 1e-8: f said 1e-9 where K alpha said 2.5e-5). So a column stops as
+// converged only by the residual at f = K alpha formed again (K read again), and
+// what stops at max_iter with another f than that goes to the batched iteration.
 #include "kmp_common.h"
 #include "kmp_kernels.h"
 #include <algorithm>
@@ -29,6 +32,9 @@ namespace kmp {
 namespace {
 constexpr int DT = 512;                 // threads of a column's workgroup
 constexpr int DW = DT / 64;
+// Times a column may meet tol with its carried f and not with K alpha. Each time it
+// goes on from the new f, and what the recurrence adds shrinks with the residual.
+constexpr int kSmallRefresh = 8;
 
 // Sum over the wavefront in every lane: rotations within the rows of 16
 // lanes, then the permlane swaps.
@@ -201,7 +207,7 @@ __global__ __launch_bounds__(DT) void small_path_kernel(const PathArrays p,
   const double ylab = p.ylab[(int64_t)g * N + i];
   if (own) mine(1) = p.ahat[row];
   double ab = p.abar[row];
-  int left = count, fl = 0, drifts = 0;
+  int left = count, fl = 0, refreshes = 0;
   for (;;) {
     const double delta = st.delta[stage], kappa = st.kappa[stage];
     const double nk = nvd * kappa, inv = 1.0 / nvd, i2d = 0.5 / delta;
@@ -346,6 +352,7 @@ __global__ __launch_bounds__(DT) void small_path_kernel(const PathArrays p,
     double f = begin && stage == 0 && fresh ? 0.0 : k_times(own ? mine(1) : 0.0);
     double fb = fresh ? f : k_times(ab);
     fresh = false;
+    bool formed = true;                           // fb is K abar itself
     // z and w at (a, fa, b), into slot k
     const auto residual = [&](int k, double a, double fa, double b) {
       double z = psi_select<LOSS>(ylab, fa + b, delta, i2d, tau) * inv;
@@ -381,33 +388,26 @@ __global__ __launch_bounds__(DT) void small_path_kernel(const PathArrays p,
       const double q2 = nvd * nvd * n2;
       if (!(q2 > 1.000001 * (tol * tol) && q2 <= 1e280)) {
         kkt = nvd * fmax(sqrt(n2), fabs(d0));
-        if (!(n2 == n2) || !(d0 == d0) || !(kkt <= 1e300)) fl = 3;
-        else if (kkt <= tol) fl = 1;
-        if (fl == 1) {
-          // certified at the extrapolated point, if f still is K alpha: an
-          // evaluation of K alpha is good to about eps n ||alpha||, so a
-          // difference of at most 16 of these stands; beyond it the column
-          // takes the new f and goes on
-          if (valid) mine(1) = ab;
+        if (!(n2 == n2) || !(d0 == d0) || !(kkt <= 1e300)) fl = 4;
+        else if (kkt <= tol) {
+          if (valid) mine(1) = ab;                // certified at the extrapolated point
           beta = bb;
-          const double a2 = sum1(valid ? ab * ab : 0.0);
-          const double fn = k_times(ab);
-          const double far = sum1(valid && !(fabs(fn - fb) <= 16.0 * 2.220446049250313e-16 * nv * sqrt(a2)) ? 1.0 : 0.0);
-          if (far != 0.0 && drifts < 3) {
-            ++drifts;
-            fl = 0;
-            f = fb = fn;
+          if (formed) fl = 1;
+          else if (++refreshes > kSmallRefresh) fl = 4;
+          else {
+            f = fb = k_times(ab);
+            formed = true;
             k = 0;
             if (own) residual(0, ab, fb, bb);
             __syncthreads();
             continue;
           }
-          if (far != 0.0) fl = 4;                 // left to the batched iteration
         }
       }
       if (fl != 0 || left <= 0) break;
       --left;
       ++total;
+      formed = false;
       const bool last = ++it >= max_iter;
       const double sa = gco * (tv - d0), db = gco * (d0 - tv);
       const double bn = bb - db, be = bn - beta;
@@ -464,7 +464,19 @@ __global__ __launch_bounds__(DT) void small_path_kernel(const PathArrays p,
       }
     }
     kkt = nvd * fmax(sqrt(n2), fabs(d0));
-    if (fl == 0 || fl >= 3 || stage + 1 >= st.n) break;
+    if (fl == 2) {
+      // the residual that the steps were taken from is that of K alpha to a
+      // hundredth, and above the rounding of a product K alpha (2 eps ||alpha||_1
+      // in every f_i): else the limit would be the carried f's and not the column's
+      const double al = own && valid ? mine(1) : 0.0;
+      const double fn = k_times(al);
+      const double dz = psi_select<LOSS>(ylab, fn + beta, delta, i2d, tau) -
+                        psi_select<LOSS>(ylab, f + beta, delta, i2d, tau);
+      const double off = sqrt(sum1(live ? dz * dz : 0.0));
+      const double rnd = 4.44e-16 * sqrt((double)nv) * (LOSS == 1 ? 0.25 : i2d) * sum1(fabs(al));
+      if (!(off <= fmax(tol, 0.01 * kkt) && kkt > 4.0 * rnd)) fl = 4;
+    }
+    if (fl == 0 || fl == 4 || stage + 1 >= st.n) break;
     fl = 0;
     ++stage;                                      // converged or at max_iter: the next stage
     fresh = true;
@@ -495,8 +507,8 @@ static int small_run(int stages, int64_t cols, int64_t same) {
   return stages == 1 ? (int)std::min(ceil_div(cols, 256), same) : 1;
 }
 
-bool small_pays(int N, int loss, int stages, int64_t cols, int64_t same) {
-  if (N > kSmallOrder || stages > kSmallStages) return false;
+bool small_pays(int N, int loss, int stages, int64_t cols, int64_t same, double least) {
+  if (N > kSmallOrder || stages > kSmallStages || least < kLeastShift) return false;
   if (loss != KMP_LOGISTIC) return true;
   const int run = small_run(stages, cols, same);
   const int64_t rounds = ceil_div(ceil_div(cols, run), 256) * (run > 1 ? 2 : 1);

@@ -11,8 +11,10 @@
 //   K Da  = g (t - d0) K v + n_v kappa (w - 2 lambda x),
 // so f follows alpha without a product with K. The iterates are those of
 // the batched form up to rounding (the inner products of its restart and KKT
-// tests do not change under the orthogonal Q). f is compared with K alpha
-// through the factor when the columns have stopped (dense_check).
+// tests do not change under the orthogonal Q). The carried f drifts as lambda
+// shrinks: it is formed again from alpha through the factor at intervals and when
+// the columns have stopped, and a column stops as converged by that f only
+// (dense_check).
 //
 // An iteration is two launches: the products of all dense columns spread over
 // the chip, then one workgroup per column for everything elementwise. An
@@ -67,6 +69,7 @@ __global__ __launch_bounds__(64) void dense_list_kernel(int G, int C, int cap,
                                                         const int* __restrict__ cmap,
                                                         const int* __restrict__ nact,
                                                         int* __restrict__ list,
+                                                        int* __restrict__ sure,
                                                         int* __restrict__ count) {
   int base = 0;
   for (int g = 0; g < G; ++g) {
@@ -75,7 +78,8 @@ __global__ __launch_bounds__(64) void dense_list_kernel(int G, int C, int cap,
       if (base + k < cap) list[base + k] = g * C + cmap[(int64_t)g * C + k];
     base += n;
   }
-  if (threadIdx.x == 0) *count = min(base, cap);
+  for (int k = threadIdx.x; k < cap; k += 64) sure[k] = 0;
+  if (threadIdx.x == 0) count[0] = min(base, cap);
 }
 
 // Y = Q M^{-1} by rows (M = 2 lambda I + B/(n_v kappa) of a column, from its
@@ -190,7 +194,7 @@ __global__ __launch_bounds__(256) void dense_vectors_kernel(
     const int* __restrict__ nv, const double* __restrict__ ahat, const double* __restrict__ abar,
     const double* __restrict__ vhat, const double* __restrict__ uvec) {
   const int t = blockIdx.y;
-  if (t >= *a.count) return;
+  if (t >= *a.count || (REFRESH && a.sure[t] == 1)) return;
   const int64_t gc = a.list[t];
   const int g = (int)(gc / C);
   const int i = 4 * (int)blockIdx.x + (threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -229,11 +233,11 @@ __global__ __launch_bounds__(DPC * DPR) void dense_project_kernel(
     int N, int C, const DenseArrays a, const double* __restrict__ Q, const int* __restrict__ nv,
     double* __restrict__ ahat, double* __restrict__ abar) {
   __shared__ double pa[DPR][DPC], pb[DPR][DPC];
-  const int t = blockIdx.y;
-  if (t >= *a.count) return;
+  const int t = blockIdx.y, j = blockIdx.x * DPC + threadIdx.x, ry = threadIdx.y;
+  if (t == 0 && j == 0 && ry == 0) a.count[1] = 0;
+  if (t >= a.count[0] || a.sure[t] == 1) return;
   const int64_t gc = a.list[t];
   const int g = (int)(gc / C), m = nv[g];
-  const int j = blockIdx.x * DPC + threadIdx.x, ry = threadIdx.y;
   const double* q = Q + (int64_t)g * N * N + j;
   const double *xa = dvec(a, N, VA, t), *xb = dvec(a, N, VAB, t);
   double s0 = 0.0, s1 = 0.0;
@@ -411,35 +415,68 @@ __global__ __launch_bounds__(DT) void dense_update_kernel(const DenseArrays a, c
       p.flag[gc] = 1;
       p.beta[gc] = bb;
     }
+    if (START) a.sure[t] = done && a.sure[t] == 2;
   }
 }
 
-// A column's f against f formed again from alpha (VX, VT). Evaluating K alpha
-// through the factor carries an error of the order of eps ||K|| ||alpha|| <=
-// eps n ||alpha||_2, so a difference of at most 16 of these keeps f; beyond
-// it the column takes the new f and, when it had converged, goes on.
-__global__ __launch_bounds__(DT) void dense_check_kernel(const DenseArrays a, const PathArrays p) {
+// A column takes the f that was formed again from its alpha (VX, VT). One that has
+// converged is active again until its residual there is known (the update with
+// START, which follows; sure: 2, then 1 if it stays converged, with nothing left to
+// check). One at max_iter must not stop there (count[1]) if the new f moves its
+// residual n_v ||z + 2 lambda alpha|| by more than tol and a hundredth of itself, or
+// if that is of the size of the rounding of a product K alpha (2 eps ||alpha||_1 in
+// every f_i).
+__global__ __launch_bounds__(DT) void dense_check_kernel(const DenseArrays a, const PathArrays p,
+                                                         double delta, double tol) {
   __shared__ double red[DW];
   const int t = blockIdx.x;
-  if (t >= *a.count) return;
+  if (t >= a.count[0] || a.sure[t] == 1) return;
   const int64_t gc = a.list[t];
   const int fl = p.flag[gc];
-  if (fl > 1) return;                             // uniform over the block
-  const int N = p.N, nv = p.nv[(int)(gc / p.C)];
-  const double *pab = dvec(a, N, VAB, t), *pn = dvec(a, N, VX, t), *pnb = dvec(a, N, VT, t);
+  if (fl > 2) return;                             // uniform over the block
+  const int N = p.N, g = (int)(gc / p.C), nv = p.nv[g];
+  const double *pa = dvec(a, N, VA, t), *pn = dvec(a, N, VX, t), *pnb = dvec(a, N, VT, t);
   double *pf = dvec(a, N, VF, t), *pfb = dvec(a, N, VFB, t);
-  double n2 = 0.0, far = 0.0;
-  for (int i = threadIdx.x; i < nv; i += DT) n2 = fma(pab[i], pab[i], n2);
-  n2 = block_sum<DW>(n2, red);
-  const double bound = 16.0 * 2.220446049250313e-16 * nv * sqrt(n2);
-  for (int i = threadIdx.x; i < nv; i += DT) far += fabs(pnb[i] - pfb[i]) <= bound ? 0.0 : 1.0;
-  far = block_sum<DW>(far, red);
-  if (far == 0.0) return;
-  for (int i = threadIdx.x; i < nv; i += DT) {
-    pf[i] = pn[i];
-    pfb[i] = pnb[i];
+  if (fl < 2) {
+    for (int i = threadIdx.x; i < nv; i += DT) {
+      pf[i] = pn[i];
+      pfb[i] = pnb[i];
+    }
+    if (threadIdx.x == 0) {
+      p.flag[gc] = 0;
+      a.sure[t] = 2 * fl;
+    }
+    return;
   }
-  if (threadIdx.x == 0) p.flag[gc] = 0;
+  const double tau = p.tau[gc], kkt = p.kkt[gc], b = p.beta[gc];
+  const int32_t hf = p.cfold ? p.cfold[gc] : -1;
+  const int32_t* rf = p.rfold ? p.rfold + (int64_t)g * N : nullptr;
+  const double* y = p.ylab + (int64_t)g * N;
+  double e = 0.0, a1 = 0.0;
+  for (int i = threadIdx.x; i < nv; i += DT) {
+    const double dz = loss_psi(p.loss, y[i], pn[i] + b, delta, tau) -
+                      loss_psi(p.loss, y[i], pf[i] + b, delta, tau);
+    if (!(rf && rf[i] == hf)) e = fma(dz, dz, e);
+    a1 += fabs(pa[i]);
+  }
+  e = sqrt(block_sum<DW>(e, red));
+  a1 = block_sum<DW>(a1, red);
+  const double rnd = 4.44e-16 * sqrt((double)nv) * (p.loss == 1 ? 0.25 : 0.5 / delta) * a1;
+  if (threadIdx.x == 0 && !(e <= fmax(tol, 0.01 * kkt) && kkt > 4.0 * rnd)) atomicAdd(a.count + 1, 1);
+}
+
+// count[1]: also the columns that are not finite. count[2]: the least number of
+// iterations of an active one.
+__global__ __launch_bounds__(64) void dense_report_kernel(const DenseArrays a, const PathArrays p) {
+  int least = INT32_MAX;
+  for (int t = threadIdx.x; t < a.count[0]; t += 64) {
+    const int64_t gc = a.list[t];
+    const int fl = p.flag[gc];
+    if (fl == 0) least = min(least, p.iters[gc]);
+    if (fl > 2) atomicAdd(a.count + 1, 1);
+  }
+  for (int off = 32; off >= 1; off >>= 1) least = min(least, __shfl_xor(least, off, 64));
+  if (threadIdx.x == 0) a.count[2] = least;
 }
 
 template <bool START>
@@ -468,7 +505,7 @@ int dense_begin(hipStream_t s, const PathArrays& p, const DenseArrays& a, int co
   int rc;
   const int N = p.N, nb = N / 64;
   hipLaunchKernelGGL(dense_list_kernel, dim3(1), dim3(64), 0, s, p.G, p.C, cols, p.cmap, p.nact,
-                     a.list, a.count);
+                     a.list, a.sure, a.count);
   KMP_LAUNCH_CHECK();
   const int64_t blocks = (int64_t)cols * nb;
   for (int64_t e0 = 0; e0 < blocks; e0 += a.yblocks) {
@@ -509,9 +546,13 @@ int dense_check(hipStream_t s, const PathArrays& p, const DenseArrays& a, int co
   hipLaunchKernelGGL((dense_vectors_kernel<true>), dim3((unsigned)(N / 4), (unsigned)cols), dim3(256),
                      0, s, N, p.C, a, p.Q, p.QB, p.nv, p.ahat, p.abar, p.vhat, p.uvec);
   KMP_LAUNCH_CHECK();
-  hipLaunchKernelGGL(dense_check_kernel, dim3((unsigned)cols), dim3(DT), 0, s, a, p);
+  hipLaunchKernelGGL(dense_check_kernel, dim3((unsigned)cols), dim3(DT), 0, s, a, p, delta, tol);
   KMP_LAUNCH_CHECK();
-  return launch_update<true>(s, p, a, cols, delta, kappa, tol, 1 << 30, 0);
+  const int rc = launch_update<true>(s, p, a, cols, delta, kappa, tol, 1 << 30, 0);
+  if (rc != 0) return rc;
+  hipLaunchKernelGGL(dense_report_kernel, dim3(1), dim3(64), 0, s, a, p);
+  KMP_LAUNCH_CHECK();
+  return 0;
 }
 
 }  // namespace kmp

@@ -359,7 +359,7 @@ int64_t dense_blocks(const Plan& p) {
 }
 
 size_t dense_column_bytes(const Plan& p) {
-  return sizeof(double) * ((size_t)p.N * p.N + (size_t)kDenseVectors * p.N + 2) + sizeof(int);
+  return sizeof(double) * ((size_t)p.N * p.N + (size_t)kDenseVectors * p.N + 2) + 2 * sizeof(int);
 }
 
 // Columns the area holds when `room` bytes are left for it.
@@ -388,7 +388,8 @@ DenseArrays carve_dense(const Plan& p, char* base, size_t room) {
   a.vec = c.take<double>(kDenseVectors * cap * N);
   a.scal = c.take<double>(2 * cap);
   a.list = c.take<int>(cap);
-  a.count = c.take<int>(1);
+  a.sure = c.take<int>(cap);
+  a.count = c.take<int>(kDenseCounts);
   a.yblocks = dense_blocks(p);
   a.Y = c.take<double>((size_t)a.yblocks * 64 * N);
   return a;
@@ -478,9 +479,11 @@ int make_plan(const kmp_path_spec* spec, int64_t n, int64_t d, int32_t L, const 
 }
 
 // Small orders: iterations of a column per launch. Dense columns: iterations
-// between two polls, and checks that find f drifted before a stage goes back
-// to the batched iteration.
-constexpr int kSmallChunk = 8192, kDensePoll = 16, kDenseChecks = 3;
+// between two polls (kDenseSoon after columns have gone on, which then take few),
+// between two checks of f while columns are active, and how often columns may stop
+// and go on before the batch goes back to the batched iteration.
+constexpr int kSmallChunk = 8192, kDensePoll = 16, kDenseSoon = 4;
+constexpr int kDenseRefresh = 512, kDenseChecks = 24;
 // Whether a stage goes on in dense form from iteration `it` with `active`
 // columns in `groups` groups: once the batched iterations have taken what
 // forming the resolvents takes (they may be needed for few iterations more;
@@ -828,7 +831,7 @@ int kmp_fit_path(void* stream, const kmp_path_spec* spec, const double* X, int64
       Bump::round(sizeof(double) * n) + Bump::round(2 * sizeof(int)) +
       Bump::round(sizeof(int32_t) * (size_t)plan.nblk * N) +
       Bump::round(sizeof(int32_t) * (size_t)V * plan.Mh) + Bump::round(sizeof(int32_t) * n) +
-      Bump::round(sizeof(int) * ((size_t)G + 2)) +
+      Bump::round(sizeof(int) * ((size_t)G + 2 + kDenseCounts)) +
       (size_t)nbatch * (2 * Bump::round(sizeof(double) * (size_t)G * C) +
                         2 * Bump::round(sizeof(int) * (size_t)G * C) +
                         Bump::round(sizeof(int) * (size_t)G)) +
@@ -948,7 +951,7 @@ int kmp_fit_path(void* stream, const kmp_path_spec* spec, const double* X, int64
   struct PollBuf {
     int* p;
     hipEvent_t ev;
-  } poll{pin.take<int>((size_t)G + 2), ctx->ev_poll};
+  } poll{pin.take<int>((size_t)G + 2 + kDenseCounts), ctx->ev_poll};
   // The first stage's factors need the band only: they are formed on a side
   // stream while the caller's stream accumulates Q, and the stage waits for
   // them. Leaving the call (also on an error) waits for the side stream.
@@ -1121,20 +1124,23 @@ int kmp_fit_path(void* stream, const kmp_path_spec* spec, const double* X, int64
       if ((rc = first_checks()) != 0) return rc;
     }
     // a3-a9: smoothing stages
+    const int64_t iters_before = total_iters;
+    bool dense_ok = dense.cap > 0, again = false;
     for (int st = 0; st < nst && !small; ++st) {
       const double delta = stage_delta(st);
       const double kappa = stage_kappa(st);
       size_t e4 = 0, e5 = 0, e6 = 0;
       if ((rc = tm.mark(s, &e4)) != 0) return rc;
-      if (st == 0)
+      if (st == 0 && !again)
         KMP_HIP_TRY(hipStreamWaitEvent(s, side.done, 0));
       else if ((rc = path_stage_factor(s, pa, kappa)) != 0)
         return rc;
       if ((rc = path_stage_vectors(s, pa, kappa)) != 0) return rc;
       if ((rc = path_compact(s, pa)) != 0) return rc;
       if ((rc = tm.mark(s, &e5)) != 0) return rc;
-      int it = 0;
-      bool dense_on = dense.cap > 0;
+      int64_t ran = 0;              // iterations launched
+      bool redo = false;            // the batch from its start in batched form
+      bool dense_on = dense_ok && 2.0 * lam_least * kappa >= kLeastShift;
       {
         IterGraph ig;
         if (use_graphs && (rc = capture_iterations(pa, delta, kappa, spec->tol, spec->max_iter,
@@ -1142,22 +1148,52 @@ int kmp_fit_path(void* stream, const kmp_path_spec* spec, const double* X, int64
           return rc;
         if ((rc = post_poll()) != 0) return rc;
         bool pending = true;
-        int dcols = 0, checks = 0;    // columns in dense form (0: the batched iteration)
+        // it: iterations of every active column
+        int it = 0, dcols = 0;        // columns in dense form (0: the batched iteration)
+        int since = 0, checks = 0, chunk = kDensePoll;
+        // f of the dense columns formed again: the active columns that leaves
+        const auto recheck = [&](int* active) -> int {
+          int r = dense_check(s, pa, dense, dcols, delta, kappa, spec->tol);
+          if (r != 0) return r;
+          int* rep = poll.p + Gb + 2;
+          KMP_HIP_TRY(hipMemcpyAsync(rep, dense.count, kDenseCounts * sizeof(int),
+                                     hipMemcpyDeviceToHost, s));
+          if ((r = poll_now(active)) != 0) return r;
+          since = 0;
+          redo = rep[1] > 0;
+          // columns that go on have had no iteration since they stopped
+          if (*active > 0) it = std::min(it, rep[2]);
+          return 0;
+        };
+        // all have stopped: alpha is back in ahat, and those that go on do so
+        const auto stopped = [&](int* active) -> int {
+          const int r = recheck(active);
+          if (r != 0) return r;
+          chunk = kDenseSoon;
+          if (++checks >= kDenseChecks) dense_on = false;
+          if (*active == 0 || !dense_on) dcols = 0;
+          return 0;
+        };
         while (it < spec->max_iter) {
           if (dcols > 0) {
-            const int count = std::min(kDensePoll, spec->max_iter - it);
+            const int count = std::min(chunk, spec->max_iter - it);
+            chunk = std::min(2 * chunk, kDensePoll);
             if ((rc = dense_iterations(s, pa, dense, dcols, delta, kappa, spec->tol, spec->max_iter,
                                        restart, count)) != 0)
               return rc;
             it += count;
+            ran += count;
+            since += count;
           } else if (ig.exec && it % spec->poll_every == 0 &&
                      it + spec->poll_every <= spec->max_iter) {
             KMP_HIP_TRY(hipGraphLaunch(ig.exec, s));
             it += spec->poll_every;
+            ran += spec->poll_every;
           } else {
             if ((rc = path_iteration(s, pa, delta, kappa, spec->tol, spec->max_iter, restart)) != 0)
               return rc;
             ++it;
+            ++ran;
             // the active lists follow every iteration (one small launch), so
             // the GEMMs drop a converged column at once; the counts still
             // come back at the polls only
@@ -1167,23 +1203,19 @@ int kmp_fit_path(void* stream, const kmp_path_spec* spec, const double* X, int64
             int active = 0;
             if ((rc = read_poll(&active)) != 0) return rc;
             pending = false;
-            if (active == 0 && dcols > 0) {
-              if ((rc = dense_check(s, pa, dense, dcols, delta, kappa, spec->tol)) != 0) return rc;
-              if ((rc = poll_now(&active)) != 0) return rc;
-              if (active > 0 && ++checks >= kDenseChecks) {   // back to the batched iteration
-                dcols = 0;
-                dense_on = false;
-              }
+            if (dcols > 0 && active > 0 && since >= kDenseRefresh) {
+              if ((rc = recheck(&active)) != 0) return rc;
+            } else {
+              if (dcols > 0 && active == 0 && (rc = stopped(&active)) != 0) return rc;
+              if (active == 0) break;
             }
-            if (active == 0) {
-              dcols = 0;                                    // alpha is back in ahat
-              break;
-            }
+            if (redo) break;
             const int groups = (int)(Gb - std::count(nact_h.begin(), nact_h.end(), 0));
             if (dense_on && dcols == 0 && active <= dense.cap && dense_pays(pa.loss, N, groups, it, active)) {
               if ((rc = path_compact(s, pa)) != 0) return rc;
               if ((rc = dense_begin(s, pa, dense, active, delta, kappa, spec->tol)) != 0) return rc;
               dcols = active;
+              since = 0;
             }
           }
           if (dcols > 0 || it % spec->poll_every == 0 || it >= spec->max_iter) {
@@ -1191,20 +1223,30 @@ int kmp_fit_path(void* stream, const kmp_path_spec* spec, const double* X, int64
             if ((rc = post_poll()) != 0) return rc;
             pending = true;
           }
+          if (it >= spec->max_iter) {
+            int active = 0;
+            if ((rc = read_poll(&active)) != 0) return rc;
+            pending = false;
+            if (dcols > 0 && (rc = stopped(&active)) != 0) return rc;
+            if (redo) break;
+          }
         }
         if (pending) {
           int active = 0;
           if ((rc = read_poll(&active)) != 0) return rc;
         }
-        // columns stopped by max_iter in dense form
-        if (dcols > 0 &&
-            (rc = dense_check(s, pa, dense, dcols, delta, kappa, spec->tol)) != 0)
-          return rc;
       }
-      total_iters += it;
+      total_iters += ran;
       if ((rc = tm.mark(s, &e6)) != 0) return rc;
       tm.span(&t_pre, e4, e5);
       tm.span(&t_path, e5, e6);
+      if (redo) {
+        if ((rc = path_init_columns(s, pa)) != 0) return rc;
+        again = true;
+        dense_ok = false;
+        total_iters = iters_before;
+        st = -1;
+      }
     }
 
     // a10: finalize

@@ -252,16 +252,19 @@ struct DenseArrays {
   double* vec = nullptr;    // kDenseVectors x cap x N
   double* scal = nullptr;   // cap x 2
   int* list = nullptr;      // cap: column of each
-  int* count = nullptr;     // 1
+  int* sure = nullptr;      // cap: 1 once a column stays converged (dense_check)
+  int* count = nullptr;     // kDenseCounts: the columns, then what a check reports
   double* Y = nullptr;
   int64_t yblocks = 0;
 };
-constexpr int kDenseVectors = 9;
+constexpr int kDenseVectors = 9, kDenseCounts = 3;
 constexpr int kDenseMaxOrder = 3072;
 // dense_begin takes the active columns (at most cols of them, cols <= cap) into
 // dense form, dense_iterations runs count iterations of those still active.
-// dense_check writes alpha back into ahat, compares f with K alpha and lets a
-// column whose f has drifted go on.
+// dense_check writes alpha back into ahat and forms f again from it, by which a
+// converged column stays converged or goes on; count[1] and count[2] report the
+// columns that must not stop as they have and the least iteration count of an
+// active one.
 int dense_begin(hipStream_t s, const PathArrays& p, const DenseArrays& a, int cols, double delta,
                 double kappa, double tol);
 int dense_iterations(hipStream_t s, const PathArrays& p, const DenseArrays& a, int cols, double delta,

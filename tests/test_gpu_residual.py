@@ -1,4 +1,4 @@
-"""What the forms that carry f = K alpha by a recurrence (small.hip) report at
+"""What the forms that carry f = K alpha by a recurrence (small.hip, dense.hip) report at
 small penalties, where the recurrence's rounding is largest: the residual
 n_v max(||z + 2 lambda alpha||_2, |1'z|) formed outside the library, in extended
 precision on the library's own kernel matrix, against the bar that a converged
@@ -65,6 +65,10 @@ def _fits(loss, n, d, sigma, data, delta, lam, max_iter):
     ("hinge", 250, 5, 20.0, "shift", 1.0, 1e-8),
     ("check", 180, 5, 3.0, "shift", 0.125, 1e-6),
     ("logistic", 180, 2, 5.0, "shift", 1.0, 1e-9),
+    ("hinge", 420, 2, 5.0, "shift", 1.0, 1e-9),
+    ("hinge", 420, 5, 3.0, "shift", 0.125, 1e-6),
+    ("check", 420, 5, 20.0, "shift", 0.125, 1e-8),
+    ("logistic", 420, 2, 5.0, "shift", 1.0, 1e-9),
 ])
 def test_a_converged_column_is_converged(loss, n, d, sigma, data, delta, lam):
     """A column reported as converged has the residual that this claims, up to the
@@ -73,7 +77,10 @@ def test_a_converged_column_is_converged(loss, n, d, sigma, data, delta, lam):
     (_, g, kkt, noise), (_, gb, kb, _) = _fits(loss, n, d, sigma, data, delta, [lam], 20000)
     print(g["status"].ravel(), g["iters"].ravel(), kkt, noise, gb["status"].ravel(), kb)
     if g["status"].ravel()[0] == 0:
-        assert kkt[0] <= TOL + noise[0], (kkt, noise)
+        # above order 256 f is formed through the factor, whose backward error the
+        # batched form's result shows
+        bar = TOL + noise[0] + (2 * kb[0] if n > 256 else 0.0)
+        assert kkt[0] <= bar, (kkt, noise, kb)
     else:
         assert gb["status"].ravel()[0] != 0 and kkt[0] <= 10 * kb[0]
 
@@ -83,6 +90,8 @@ def test_a_converged_column_is_converged(loss, n, d, sigma, data, delta, lam):
     ("hinge", 250, 2, 5.0, "random", 0.125, 1e-13, 3000),
     ("check", 60, 5, 20.0, "shift", 1.0, 1e-12, 3000),
     ("logistic", 120, 5, 20.0, "random", 1.0, 1e-13, 3000),
+    ("hinge", 420, 2, 5.0, "shift", 0.125, 1e-12, 3000),
+    ("check", 420, 5, 20.0, "random", 0.125, 1e-13, 3000),
 ])
 def test_max_iter_with_another_f(loss, n, d, sigma, data, delta, lam, max_iter):
     """A column whose carried f is not K alpha any more is not stopped by max_iter
@@ -103,3 +112,19 @@ def test_more_iterations_than_one_launch():
     print(g["status"].ravel(), g["iters"].ravel(), kkt, noise, gb["iters"].ravel(), kb)
     assert c == cb == 0 and g["iters"].max() > 8192 and g["timings"]["factor_ms"] == 0
     assert np.all(kkt <= TOL + noise), (kkt, noise)
+
+
+@pytest.mark.parametrize("n", [180, 420])
+def test_stopped_by_max_iter_means_that_many_iterations(n):
+    """Columns that stop as converged by their carried f and go on near max_iter:
+    no column is reported as stopped by max_iter after fewer iterations."""
+    announce(f"iterations of columns stopped by max_iter n={n}")
+    lam = [1e-6, 1e-5, 1e-4]
+    _, g, _, _ = _fits("hinge", n, 5, 3.0, "shift", 0.125, lam, 20000)[0]
+    assert np.all(g["status"] == 0)
+    most = int(g["iters"].max())
+    for limit in (most - 1, most - 20, most // 2, most):
+        for code, g, kkt, _ in _fits("hinge", n, 5, 3.0, "shift", 0.125, lam, limit):
+            st, it = g["status"].ravel(), g["iters"].ravel()
+            print(limit, st, it, kkt)
+            assert np.all(it[st == 1] == limit) and np.all(it <= limit) and np.all(st <= 1)

@@ -198,7 +198,8 @@ size_t kmp_workspace_bytes(const kmp_path_spec* spec, int64_t n, int64_t d,
  *   fold_id  HOST, n ids in [0, V); every fold non-empty; for hinge and
  *            logistic every training set must contain both classes
  *   workspace DEVICE, >= kmp_workspace_bytes(..., sigma_batch) for some
- *            sigma_batch; the largest batch that fits is used
+ *            sigma_batch; the largest batch whose size without the
+ *            optional part fits is used, and the rest for that part
  * Outputs (DEVICE unless stated; index order [s][q][v][l], s fastest-slowest
  * as written, i.e. cell (s,q,v,l) at ((s*Q + q)*V + v)*L + l):
  *   alpha    [S][Q][V][L][n]; zeros at the held-out indices of fold v

@@ -107,3 +107,14 @@ def test_dense_stops_at_max_iter(n, max_iter):
     assert np.array_equal(a["status"], b["status"]) and np.array_equal(a["iters"], b["iters"])
     scale = np.abs(b["alpha"]).max(axis=-1, keepdims=True)
     assert np.all(np.abs(a["alpha"] - b["alpha"]) <= ALPHA_RTOL * scale)
+
+
+@pytest.mark.parametrize("L", [5, 20])
+def test_workspace_for_fewer_bandwidths(L):
+    """Three bandwidths in a workspace sized for one: a larger batch with fewer
+    dense columns or none, the same results."""
+    inp = W.small_problem("hinge", 450, 4, seed=8, V=3, L=L, lam_lo=-3.0, lam_hi=0.0)
+    inp["sigmas"] = np.asarray(inp["sigmas"])[0] * np.array([1.0, 0.5, 2.0])
+    announce(f"workspace sized for one bandwidth of three, L={L}")
+    one, _ = _both(inp, "hinge", sigma_batch=1)
+    _agree(one, _both(inp, "hinge")[1])

@@ -835,7 +835,7 @@ int kmp_fit_path(void* stream, const kmp_path_spec* spec, const double* X, int64
       Bump::round(sizeof(double) * n) + Bump::round(2 * sizeof(int)) +
       Bump::round(sizeof(int32_t) * (size_t)plan.nblk * N) +
       Bump::round(sizeof(int32_t) * (size_t)V * plan.Mh) + Bump::round(sizeof(int32_t) * n) +
-      Bump::round(sizeof(int) * ((size_t)G + 2 + kDenseCounts)) +
+      Bump::round(sizeof(int) * ((size_t)G + 1 + kDenseCounts)) +
       (size_t)nbatch * (2 * Bump::round(sizeof(double) * (size_t)G * C) +
                         2 * Bump::round(sizeof(int) * (size_t)G * C) +
                         Bump::round(sizeof(int) * (size_t)G)) +
@@ -955,7 +955,7 @@ int kmp_fit_path(void* stream, const kmp_path_spec* spec, const double* X, int64
   struct PollBuf {
     int* p;
     hipEvent_t ev;
-  } poll{pin.take<int>((size_t)G + 2 + kDenseCounts), ctx->ev_poll};
+  } poll{pin.take<int>((size_t)G + 1 + kDenseCounts), ctx->ev_poll};
   // The first stage's factors need the band only: they are formed on a side
   // stream while the caller's stream accumulates Q, and the stage waits for
   // them. Leaving the call (also on an error) waits for the side stream.
@@ -1063,7 +1063,7 @@ int kmp_fit_path(void* stream, const kmp_path_spec* spec, const double* X, int64
     // converged, that iteration finds nothing to do and the stage ends).
     const auto post_poll = [&]() -> int {
       KMP_HIP_TRY(hipMemcpyAsync(poll.p, lay.nact, sizeof(int) * Gb, hipMemcpyDeviceToHost, s));
-      KMP_HIP_TRY(hipMemcpyAsync(poll.p + Gb, lay.active, 2 * sizeof(int), hipMemcpyDeviceToHost, s));
+      KMP_HIP_TRY(hipMemcpyAsync(poll.p + Gb, lay.active, sizeof(int), hipMemcpyDeviceToHost, s));
       KMP_HIP_TRY(hipEventRecord(poll.ev, s));
       return 0;
     };
@@ -1089,18 +1089,17 @@ int kmp_fit_path(void* stream, const kmp_path_spec* spec, const double* X, int64
         ss.delta[st] = stage_delta(st);
         ss.kappa[st] = stage_kappa(st);
       }
-      PathArrays pt = pa;
-      pt.iters = lay.iters_total;
       int active = Gb * C, most = 0;
       for (bool begin = true; active > 0; begin = false) {
         if ((rc = small_path(s, pa, lay.A, ss, spec->tol, spec->max_iter, restart, kSmallChunk,
                              begin, L)) != 0)
           return rc;
         if (begin && (rc = first_checks()) != 0) return rc;
-        if ((rc = path_compact(s, pt)) != 0) return rc;
-        if ((rc = post_poll()) != 0) return rc;
-        if ((rc = read_poll(&active)) != 0) return rc;
-        most = poll.p[Gb + 1];
+        KMP_HIP_TRY(hipMemcpyAsync(poll.p, lay.active, 2 * sizeof(int), hipMemcpyDeviceToHost, s));
+        KMP_HIP_TRY(hipEventRecord(poll.ev, s));
+        KMP_HIP_TRY(hipEventSynchronize(poll.ev));
+        active = poll.p[0];
+        most = poll.p[1];
         if (most == INT32_MAX) break;
       }
       // a column whose f would not settle on K alpha: this batch in batched form
@@ -1159,7 +1158,7 @@ int kmp_fit_path(void* stream, const kmp_path_spec* spec, const double* X, int64
         const auto recheck = [&](int* active) -> int {
           int r = dense_check(s, pa, dense, dcols, delta, kappa, spec->tol);
           if (r != 0) return r;
-          int* rep = poll.p + Gb + 2;
+          int* rep = poll.p + Gb + 1;
           KMP_HIP_TRY(hipMemcpyAsync(rep, dense.count, kDenseCounts * sizeof(int),
                                      hipMemcpyDeviceToHost, s));
           if ((r = poll_now(active)) != 0) return r;

@@ -219,7 +219,7 @@ struct PathArrays {
   int* flag = nullptr;
   int* iters = nullptr;     // per stage
   int* iters_total = nullptr;
-  int* active_count = nullptr;  // 2 ints
+  int* active_count = nullptr;  // 2 ints, the second by small_path only
   int* cmap = nullptr;      // G x C: the active columns of each group, in order
   int* nact = nullptr;      // G: number of active columns of each group
   const int* nv_host = nullptr;  // G valid rows (host), for the work counters
@@ -235,8 +235,7 @@ int path_stage_vectors(hipStream_t s, const PathArrays& p, double kappa);
 int path_iteration(hipStream_t s, const PathArrays& p, double delta, double kappa, double tol,
                    int max_iter, int restart);
 // Rebuilds cmap/nact from the column flags and writes the total number of
-// active columns and the largest of the columns' iteration counts (the
-// largest int if a column has flag 4) to active_count (2 ints). The path GEMMs compute only the columns
+// active columns to active_count. The path GEMMs compute only the columns
 // listed in cmap, so it runs after every change of the flags that should
 // shrink the GEMMs (stage start, polls).
 int path_compact(hipStream_t s, const PathArrays& p);
@@ -276,7 +275,8 @@ int dense_check(hipStream_t s, const PathArrays& p, const DenseArrays& a, int co
 // factorisation; ahat and abar hold alpha and its extrapolation in observation
 // space. begin: the first launch (flags 0, ahat 0). Columns that count stops
 // stay active for a further launch; flag 4 marks one whose carried f would not
-// settle on K alpha or is not finite.
+// settle on K alpha or is not finite. active_count then holds the active columns
+// and the largest iters_total of any (the largest int if one has flag 4).
 constexpr int kSmallOrder = 256, kSmallStages = 8;
 struct SmallStages {
   int n = 0;

@@ -1682,20 +1682,17 @@ int path_iteration(hipStream_t s, const PathArrays& p, double delta, double kapp
 // in a fixed order for the total.
 __global__ __launch_bounds__(PB) void compact_columns_kernel(int G, int C,
                                                              const int* __restrict__ flag,
-                                                             const int* __restrict__ iters,
                                                              int* __restrict__ cmap,
                                                              int* __restrict__ nact,
                                                              int* __restrict__ total) {
-  __shared__ int cnt[PW], most[PB];
+  __shared__ int cnt[PW];
   const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  int mine = 0, mi = 0;
+  int mine = 0;
   for (int g = wv; g < G; g += PW) {
     int base = 0;
     for (int c0 = 0; c0 < C; c0 += 64) {
       const int c = c0 + lane;
       const bool act = c < C && flag[(int64_t)g * C + c] == 0;
-      if (c < C)
-        mi = max(mi, flag[(int64_t)g * C + c] == 4 ? 0x7fffffff : iters[(int64_t)g * C + c]);
       const unsigned long long m = __ballot(act);
       const int rank = __popcll(m & ((1ull << lane) - 1ull));
       if (act) cmap[(int64_t)g * C + base + rank] = c;
@@ -1705,23 +1702,17 @@ __global__ __launch_bounds__(PB) void compact_columns_kernel(int G, int C,
     mine += base;
   }
   if (lane == 0) cnt[wv] = mine;
-  most[threadIdx.x] = mi;
   __syncthreads();
   if (threadIdx.x == 0) {
     int t = 0;
     for (int w = 0; w < PW; ++w) t += cnt[w];
-    total[0] = t;
-  }
-  if (wv == 0) {
-    for (int q = 64; q < PB; q += 64) mi = max(mi, most[q + lane]);
-    for (int off = 32; off >= 1; off >>= 1) mi = max(mi, __shfl_xor(mi, off, 64));
-    if (lane == 0) total[1] = mi;
+    *total = t;
   }
 }
 
 int path_compact(hipStream_t s, const PathArrays& p) {
-  hipLaunchKernelGGL(compact_columns_kernel, dim3(1), dim3(PB), 0, s, p.G, p.C, p.flag, p.iters,
-                     p.cmap, p.nact, p.active_count);
+  hipLaunchKernelGGL(compact_columns_kernel, dim3(1), dim3(PB), 0, s, p.G, p.C, p.flag, p.cmap,
+                     p.nact, p.active_count);
   KMP_LAUNCH_CHECK();
   return 0;
 }

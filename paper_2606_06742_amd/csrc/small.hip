@@ -498,6 +498,37 @@ __global__ __launch_bounds__(DT) void small_path_kernel(const PathArrays p,
   }
   }
 }
+
+// total[0]: columns still active; total[1]: the largest iters of any column, the
+// largest int if one has flag 4.
+__global__ __launch_bounds__(1024) void small_report_kernel(int64_t cols, const int* __restrict__ flag,
+                                                            const int* __restrict__ iters,
+                                                            int* __restrict__ total) {
+  __shared__ int part[2][16];
+  int act = 0, most = 0;
+  for (int64_t c = threadIdx.x; c < cols; c += 1024) {
+    const int fl = flag[c];
+    act += fl == 0 ? 1 : 0;
+    most = max(most, fl == 4 ? INT32_MAX : iters[c]);
+  }
+  for (int off = 32; off >= 1; off >>= 1) {
+    act += __shfl_xor(act, off, 64);
+    most = max(most, __shfl_xor(most, off, 64));
+  }
+  if ((threadIdx.x & 63) == 0) {
+    part[0][threadIdx.x >> 6] = act;
+    part[1][threadIdx.x >> 6] = most;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < 16; ++w) {
+      act += part[0][w];
+      most = max(most, part[1][w]);
+    }
+    total[0] = act;
+    total[1] = most;
+  }
+}
 }  // namespace
 
 // One column a workgroup while its stages differ in R; with one stage the
@@ -540,6 +571,9 @@ int small_path(hipStream_t s, const PathArrays& p, const double* K, const SmallS
   // iterations is not known here)
   const double n = (double)p.N;
   kc_end(KMP_KC_UPDATE, s, 8.0 * cols * (n * n + 6.0 * n), 2.0 * cols * st.n * n * n * n);
+  hipLaunchKernelGGL(small_report_kernel, dim3(1), dim3(1024), 0, s, cols, p.flag, p.iters_total,
+                     p.active_count);
+  KMP_LAUNCH_CHECK();
   return 0;
 }
 

@@ -488,17 +488,21 @@ constexpr int kDenseRefresh = 512, kDenseChecks = 24;
 // columns in `groups` groups: once the batched iterations have taken what
 // forming the resolvents takes (they may be needed for few iterations more;
 // eight are granted), and for the logistic loss, whose columns stop after tens
-// of iterations (44 at most over 750 cells at n = 2000, where two columns taken
-// over near the end cost 0.5 of 21 ms), six times that. Times in us, measured
-// over orders 320 to 2048 and 1 to 200 columns: a batched iteration takes 35 at
-// order 320, 57 at 832, 82 at 1536 and 105 at 2048 (from there its two products
-// read every group's factors at 5 TB/s), a dense one 10 and the resolvents at
-// 8 TB/s.
+// of iterations, twelve times that (44 at most at penalties from 1e-4, orders 320
+// to 1000: with six times it was taken up as the last columns stopped, 2855 to
+// 2900 us at order 384, 3537 to 3647 at 512). Times in us, measured over orders
+// 320 to 3072 and 1 to 318 columns: a batched iteration takes 33 at order 320, 48 to
+// 57 at 832, 76 to 86 at 1536 and 94 to 112 at 2048 (from there its two products
+// read every group's factors at 5 TB/s), a dense one 9 with one column of order
+// 320, 46 with 318, 45 with 47 of order 832 and with 3 of 3072 (10 and the
+// resolvents at 8 TB/s). With the forming counted 1.5 and 2.5 times, hinge and check
+// fits of orders 320 to 3072 took 1 and 3 % more. What is lost where the last columns
+// stop soon after is at most the forming: 2 of 73 ms at order 3072 and tol = 1e-4.
 bool dense_pays(int loss, int N, int groups, int it, int64_t active) {
   const double n = N, k = (double)active;
   const double batched = std::max(24.0 + 0.04 * n, groups * 16.0 * n * n / 5e6);
   const double dns = 9.0 + 0.003 * n + k * n * n * 1e-6;
-  const double form = (120.0 + 0.13 * n + k * n * n * n / 25e6) * (loss == KMP_LOGISTIC ? 6.0 : 1.0);
+  const double form = (120.0 + 0.13 * n + k * n * n * n / 25e6) * (loss == KMP_LOGISTIC ? 12.0 : 1.0);
   return (it + 8) * (batched - dns) >= form;
 }
 

@@ -118,3 +118,24 @@ def test_workspace_for_fewer_bandwidths(L):
     announce(f"workspace sized for one bandwidth of three, L={L}")
     one, _ = _both(inp, "hinge", sigma_batch=1)
     _agree(one, _both(inp, "hinge")[1])
+
+
+@pytest.mark.parametrize("loss,n,V,L,mode,taken", [
+    ("hinge", 701, 3, 7, {}, True),
+    ("check", 333, 4, 7, {"shared": True}, True),
+    ("logistic", 760, 3, 40, {}, False),     # tens of iterations: over before it would pay
+])
+def test_dense_form_is_taken_where_it_pays(loss, n, V, L, mode, taken):
+    """Every batched iteration has one loss product and one update, a dense one an
+    update only."""
+    from paper_2606_06742_amd import kmpath as km
+    device()
+    inp = W.small_problem(loss, n, 12, seed=n, V=V, L=L, lam_lo=-4.0, lam_hi=0.0)
+    announce(f"dense form taken: loss={loss} n={n} {mode}")
+    r = km.PathRunner(inp["X"], inp["y"], loss, inp["sigmas"], inp["lambdas"], inp["fold_id"], V,
+                      taus=inp["taus"] if loss == "check" else None, eager=True,
+                      kernel_timing=("update", "gemm_f"), **mode)
+    assert r.run() == 0
+    seen = dict(zip(km.KERNEL_CLASSES, r.timings.kernel_seen))
+    print(seen["update"], seen["gemm_f"], r.iters.max().item())
+    assert (seen["update"] > seen["gemm_f"]) == taken and seen["gemm_f"] > 0

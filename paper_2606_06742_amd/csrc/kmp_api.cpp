@@ -487,7 +487,7 @@ constexpr int kDenseRefresh = 512, kDenseChecks = 24;
 // Whether a stage goes on in dense form from iteration `it` with `active`
 // columns in `groups` groups: once the batched iterations have taken what
 // forming the resolvents takes (they may be needed for few iterations more;
-// eight are granted), and for the logistic loss, whose columns stop after tens
+// eight are granted, none beyond max_iter), and for the logistic loss, whose columns stop after tens
 // of iterations, twelve times that (44 at most at penalties from 1e-4, orders 320
 // to 1000: with six times it was taken up as the last columns stopped, 2855 to
 // 2900 us at order 384, 3537 to 3647 at 512). Times in us, measured over orders
@@ -498,12 +498,12 @@ constexpr int kDenseRefresh = 512, kDenseChecks = 24;
 // resolvents at 8 TB/s). With the forming counted 1.5 and 2.5 times, hinge and check
 // fits of orders 320 to 3072 took 1 and 3 % more. What is lost where the last columns
 // stop soon after is at most the forming: 2 of 73 ms at order 3072 and tol = 1e-4.
-bool dense_pays(int loss, int N, int groups, int it, int64_t active) {
+bool dense_pays(int loss, int N, int groups, int it, int left, int64_t active) {
   const double n = N, k = (double)active;
   const double batched = std::max(24.0 + 0.04 * n, groups * 16.0 * n * n / 5e6);
   const double dns = 9.0 + 0.003 * n + k * n * n * 1e-6;
   const double form = (120.0 + 0.13 * n + k * n * n * n / 25e6) * (loss == KMP_LOGISTIC ? 12.0 : 1.0);
-  return (it + 8) * (batched - dns) >= form;
+  return std::min(it + 8, left) * (batched - dns) >= form;
 }
 
 // Phase times from HIP events: mark() records an event on the stream (a
@@ -907,7 +907,22 @@ int kmp_fit_path(void* stream, const kmp_path_spec* spec, const double* X, int64
     return spec->loss == KMP_LOGISTIC ? 4.0 : 2.0 * stage_delta(st);
   };
   const double delta_final = stage_delta(nst - 1);
+  // Whether the forms that carry f = K alpha by a recurrence with explicit resolvents
+  // (small.hip, dense.hip) are used at a stage, by the fit's least penalty:
+  //  - the shift of K/n_v in a resolvent's matrix, whose inverse times the rounding is
+  //    the error of both, is at least 1e-9 (where it is 1e-11 a column of 180 rows
+  //    stayed at a residual of 90 and the batched iteration came to 5e-3);
+  //  - the rounding of a product K alpha, eps ||alpha||_2 in an f_i with ||alpha||_2 <=
+  //    1/(2 lambda sqrt(n)), is below half of tol in the residual: at tol = 1e-9 and
+  //    delta = 1/64 for penalties from 7.1e-6. Below, columns do not get to tol so,
+  //    which the batched iteration in the basis of its factor does (fits of orders 256
+  //    to 832 at penalties from 1e-6 took up to 1.4 times as long, both ways in turn).
   const double lam_least = *std::min_element(lambdas, lambdas + L);
+  const auto carries_f = [&](int st) {
+    const double slope = spec->loss == KMP_LOGISTIC ? 0.25 : 0.5 / stage_delta(st);
+    return 2.0 * lam_least * stage_kappa(st) >= 1e-9 &&
+           kEps * slope / (2.0 * lam_least) <= 0.5 * spec->tol;
+  };
 
   // host-side index lists and per-column parameters
   // row lists: the training points of each fold, or (shared factor) every
@@ -1084,7 +1099,7 @@ int kmp_fit_path(void* stream, const kmp_path_spec* spec, const double* X, int64
     };
     tm.span(&t_gram, e1, e2);
     // small orders: every column in one workgroup, from K itself
-    bool small = small_pays(N, spec->loss, nst, (int64_t)Gb * C, C / L, 2.0 * lam_least * stage_kappa(nst - 1)) &&
+    bool small = small_pays(N, spec->loss, nst, (int64_t)Gb * C, C / L) && carries_f(nst - 1) &&
                  (spec->flags & KMP_FLAG_GLOBAL_SOLVE) == 0;
     if (small) {
       SmallStages ss;
@@ -1147,7 +1162,7 @@ int kmp_fit_path(void* stream, const kmp_path_spec* spec, const double* X, int64
       if ((rc = tm.mark(s, &e5)) != 0) return rc;
       int64_t ran = 0;              // iterations launched
       bool redo = false;            // the batch from its start in batched form
-      bool dense_on = dense_ok && 2.0 * lam_least * kappa >= kLeastShift;
+      bool dense_on = dense_ok && carries_f(st);
       {
         IterGraph ig;
         if (use_graphs && (rc = capture_iterations(pa, delta, kappa, spec->tol, spec->max_iter,
@@ -1218,7 +1233,8 @@ int kmp_fit_path(void* stream, const kmp_path_spec* spec, const double* X, int64
             }
             if (redo) break;
             const int groups = (int)(Gb - std::count(nact_h.begin(), nact_h.end(), 0));
-            if (dense_on && dcols == 0 && active <= dense.cap && dense_pays(pa.loss, N, groups, it, active)) {
+            if (dense_on && dcols == 0 && active <= dense.cap &&
+                dense_pays(pa.loss, N, groups, it, spec->max_iter - it, active)) {
               if ((rc = path_compact(s, pa)) != 0) return rc;
               if ((rc = dense_begin(s, pa, dense, active, delta, kappa, spec->tol)) != 0) return rc;
               dcols = active;

@@ -243,6 +243,7 @@ int group_ones_projection(hipStream_t s, const double* Q, const int* nv, int G, 
 // QB = Q B for G groups (Q, QB: N x N row-major each; band as in PathArrays).
 int form_qb(hipStream_t s, const double* Q, const double* band, int N, int G, double* QB);
 
+constexpr double kEps = 2.220446049250313e-16;
 // The dense columns (dense.hip): cap columns' resolvents and vectors, and
 // scratch for yblocks blocks of 64 rows of N doubles while they are formed.
 struct DenseArrays {
@@ -282,20 +283,14 @@ struct SmallStages {
   int n = 0;
   double delta[kSmallStages], kappa[kSmallStages];
 };
-// The least 2 lambda kappa, the shift of K/n_v in a resolvent's matrix, with which
-// an explicit resolvent and the recurrence for f are used: the errors of both are
-// its inverse times the rounding. Below (the smallest penalties of a fit at its
-// last smoothing level) the steps themselves are too far off: at 1e-11 a column
-// of 180 rows stayed at a residual of 90 where the batched iteration came to 5e-3.
-constexpr double kLeastShift = 1e-9;
-// Whether a fit of `cols` columns, `same` of them with one group and penalty and
-// `least` the least 2 lambda kappa of any, goes this way. The hinge and check losses take hundreds of iterations a
+// Whether a fit of `cols` columns, `same` of them with one group and penalty,
+// goes this way. The hinge and check losses take hundreds of iterations a
 // column and always gain (5000 leave-one-out columns of 250 rows: 189 ms with
 // the factorisation, 91 without). The logistic loss takes tens, so the sweeps
 // decide where each compute unit forms many resolvents: five folds of 310 rows
 // (order 256) take 2.08 ms (2.62 batched) at 2 each, 3.73 (2.93) at 4, of 230
 // rows (order 192) 3.98 (4.75) at 16, growing by 0.23 (0.17) each.
-bool small_pays(int N, int loss, int stages, int64_t cols, int64_t same, double least);
+bool small_pays(int N, int loss, int stages, int64_t cols, int64_t same);
 int small_path(hipStream_t s, const PathArrays& p, const double* K, const SmallStages& st, double tol,
                int max_iter, int restart, int count, bool begin, int L);
 // One step of the path on a caller's K by a Cholesky factor per column

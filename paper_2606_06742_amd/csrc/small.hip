@@ -465,16 +465,15 @@ __global__ __launch_bounds__(DT) void small_path_kernel(const PathArrays p,
     }
     kkt = nvd * fmax(sqrt(n2), fabs(d0));
     if (fl == 2) {
-      // the residual that the steps were taken from is that of K alpha to a
-      // hundredth, and above the rounding of a product K alpha (2 eps ||alpha||_1
-      // in every f_i): else the limit would be the carried f's and not the column's
+      // the limit has to be the column's: its residual mostly that of K alpha, and
+      // above the rounding of such a product (eps ||alpha||_2 in an f_i)
       const double al = own && valid ? mine(1) : 0.0;
       const double fn = k_times(al);
       const double dz = psi_select<LOSS>(ylab, fn + beta, delta, i2d, tau) -
                         psi_select<LOSS>(ylab, f + beta, delta, i2d, tau);
       const double off = sqrt(sum1(live ? dz * dz : 0.0));
-      const double rnd = 4.44e-16 * sqrt((double)nv) * (LOSS == 1 ? 0.25 : i2d) * sum1(fabs(al));
-      if (!(off <= fmax(tol, 0.01 * kkt) && kkt > 4.0 * rnd)) fl = 4;
+      const double rnd = kEps * (LOSS == 1 ? 0.25 : i2d) * sqrt(nv * sum1(al * al));
+      if (!(off <= fmax(tol, 0.3 * kkt) && kkt > 4.0 * rnd)) fl = 4;
     }
     if (fl == 0 || fl == 4 || stage + 1 >= st.n) break;
     fl = 0;
@@ -538,8 +537,8 @@ static int small_run(int stages, int64_t cols, int64_t same) {
   return stages == 1 ? (int)std::min(ceil_div(cols, 256), same) : 1;
 }
 
-bool small_pays(int N, int loss, int stages, int64_t cols, int64_t same, double least) {
-  if (N > kSmallOrder || stages > kSmallStages || least < kLeastShift) return false;
+bool small_pays(int N, int loss, int stages, int64_t cols, int64_t same) {
+  if (N > kSmallOrder || stages > kSmallStages) return false;
   if (loss != KMP_LOGISTIC) return true;
   const int run = small_run(stages, cols, same);
   const int64_t rounds = ceil_div(ceil_div(cols, run), 256) * (run > 1 ? 2 : 1);

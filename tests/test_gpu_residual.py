@@ -26,7 +26,7 @@ def _problem(loss, n, d, data):
     return X, np.where(X[:, 0] + 0.3 * rng.standard_normal(n) > 0, 1.0, -1.0)
 
 
-def _fits(loss, n, d, sigma, data, delta, lam, max_iter):
+def _fits(loss, n, d, sigma, data, delta, lam, max_iter, restart=True):
     """Full-data fits at the penalties lam by the library's own choice of form
     and in batched form: results, residuals and what rounding adds to these."""
     import torch
@@ -45,6 +45,8 @@ def _fits(loss, n, d, sigma, data, delta, lam, max_iter):
                           refit=True, taus=np.array([0.5]) if loss == "check" else None,
                           max_iter=max_iter, delta0=delta, n_stages=1)
         r.spec.flags |= flag
+        if not restart:
+            r.spec.flags &= ~km.KMP_FLAG_RESTART
         code = r.run()
         g = r.results()
         kkt, noise = [], []
@@ -77,9 +79,9 @@ def test_a_converged_column_is_converged(loss, n, d, sigma, data, delta, lam):
     (_, g, kkt, noise), (_, gb, kb, _) = _fits(loss, n, d, sigma, data, delta, [lam], 20000)
     print(g["status"].ravel(), g["iters"].ravel(), kkt, noise, gb["status"].ravel(), kb)
     if g["status"].ravel()[0] == 0:
-        # above order 256 f is formed through the factor, whose backward error the
-        # batched form's result shows
-        bar = TOL + noise[0] + (2 * kb[0] if n > 256 else 0.0)
+        # f formed through the factor (where one was made) has the factor's backward
+        # error, which the batched form's result shows
+        bar = TOL + noise[0] + (2 * kb[0] if g["timings"]["factor_ms"] > 0 else 0.0)
         assert kkt[0] <= bar, (kkt, noise, kb)
     else:
         assert gb["status"].ravel()[0] != 0 and kkt[0] <= 10 * kb[0]
@@ -107,8 +109,8 @@ def test_max_iter_with_another_f(loss, n, d, sigma, data, delta, lam, max_iter):
 def test_more_iterations_than_one_launch():
     """A column of more than 8192 iterations goes on in further launches."""
     announce("small order, several launches of a column")
-    (c, g, kkt, noise), (cb, gb, kb, _) = _fits("hinge", 100, 5, 1.0, "random", 1.0 / 64, [1e-7, 1e-2],
-                                               60000)
+    (c, g, kkt, noise), (cb, gb, kb, _) = _fits("logistic", 100, 5, 0.5, "random", 1.0, [1e-7, 1e-2],
+                                               60000, restart=False)
     print(g["status"].ravel(), g["iters"].ravel(), kkt, noise, gb["iters"].ravel(), kb)
     assert c == cb == 0 and g["iters"].max() > 8192 and g["timings"]["factor_ms"] == 0
     assert np.all(kkt <= TOL + noise), (kkt, noise)

@@ -1099,15 +1099,18 @@ int kmp_fit_path(void* stream, const kmp_path_spec* spec, const double* X, int64
     };
     tm.span(&t_gram, e1, e2);
     // small orders: every column in one workgroup, from K itself
-    bool small = small_pays(N, spec->loss, nst, (int64_t)Gb * C, C / L) && carries_f(nst - 1) &&
-                 (spec->flags & KMP_FLAG_GLOBAL_SOLVE) == 0;
+    SmallStages ss;
+    ss.n = std::min(nst, kSmallStages);
+    for (int st = 0; st < ss.n; ++st) {
+      ss.delta[st] = stage_delta(st);
+      ss.kappa[st] = stage_kappa(st);
+    }
+    SmallFit sf;
+    sf.N = N; sf.loss = spec->loss; sf.groups = Gb; sf.L = L; sf.max_iter = spec->max_iter;
+    sf.cols = (int64_t)Gb * C; sf.same = C / L; sf.lambdas = lambdas; sf.tol = spec->tol;
+    bool small = (spec->flags & KMP_FLAG_GLOBAL_SOLVE) == 0 && carries_f(nst - 1) &&
+                 small_pays(sf, nst, ss.delta, ss.kappa);
     if (small) {
-      SmallStages ss;
-      ss.n = nst;
-      for (int st = 0; st < nst; ++st) {
-        ss.delta[st] = stage_delta(st);
-        ss.kappa[st] = stage_kappa(st);
-      }
       int active = Gb * C, most = 0;
       for (bool begin = true; active > 0; begin = false) {
         if ((rc = small_path(s, pa, lay.A, ss, spec->tol, spec->max_iter, restart, kSmallChunk,

@@ -283,14 +283,15 @@ struct SmallStages {
   int n = 0;
   double delta[kSmallStages], kappa[kSmallStages];
 };
-// Whether a fit of `cols` columns, `same` of them with one group and penalty,
-// goes this way. The hinge and check losses take hundreds of iterations a
-// column and always gain (5000 leave-one-out columns of 250 rows: 189 ms with
-// the factorisation, 91 without). The logistic loss takes tens, so the sweeps
-// decide where each compute unit forms many resolvents: five folds of 310 rows
-// (order 256) take 2.08 ms (2.62 batched) at 2 each, 3.73 (2.93) at 4, of 230
-// rows (order 192) 3.98 (4.75) at 16, growing by 0.23 (0.17) each.
-bool small_pays(int N, int loss, int stages, int64_t cols, int64_t same);
+// Whether a fit goes this way: `cols` columns in `groups` groups of order N, `same`
+// of them with one group and penalty, and the smoothing levels of its stages.
+struct SmallFit {
+  int N = 0, loss = 0, groups = 0, L = 0, max_iter = 0;
+  int64_t cols = 0, same = 0;
+  const double* lambdas = nullptr;
+  double tol = 0.0;
+};
+bool small_pays(const SmallFit& f, int stages, const double* delta, const double* kappa);
 int small_path(hipStream_t s, const PathArrays& p, const double* K, const SmallStages& st, double tol,
                int max_iter, int restart, int count, bool begin, int L);
 // One step of the path on a caller's K by a Cholesky factor per column

@@ -25,6 +25,7 @@
 #include "kmp_common.h"
 #include "kmp_kernels.h"
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 namespace kmp {
@@ -537,12 +538,47 @@ static int small_run(int stages, int64_t cols, int64_t same) {
   return stages == 1 ? (int)std::min(ceil_div(cols, 256), same) : 1;
 }
 
-bool small_pays(int N, int loss, int stages, int64_t cols, int64_t same) {
-  if (N > kSmallOrder || stages > kSmallStages) return false;
-  if (loss != KMP_LOGISTIC) return true;
-  const int run = small_run(stages, cols, same);
-  const int64_t rounds = ceil_div(ceil_div(cols, run), 256) * (run > 1 ? 2 : 1);
-  return N <= 128 || rounds <= (N <= 192 ? 24 : 2);
+// Times in us. The hinge and check losses' iterations in a stage are taken as 0.27
+// ln(1/tol) times the square root of the condition 1 + 1/(2 lambda kappa) of the
+// majorised problem, for the check loss, whose columns the few points in its
+// quadratic zone hold back, between 5 and 14 over the root of delta. Here a compute
+// unit forms a resolvent after the other (12, 110, 215 and 850 by order) and takes
+// 0.8, 1.1, 1.6 and 3.6 an iteration; in batched form the factorisation, then every
+// column's iteration at its share of the products and the slowest column's launches.
+// Fitted to 640 fits of 60 to 310 rows, 50 to 20000 columns in 1 to 30 groups,
+// penalties 1e-4 to 100, tol 1e-2 to 1e-9, one or three stages, max_iter 20 to
+// 100000, both ways: the worse form is taken by more than 10 % in 12 of them (5000
+// columns of order 256 at tol = 1e-2: 16 ms batched, 67 here; by default 115 and 34).
+// The logistic loss takes tens of iterations, so the resolvents decide (order 256:
+// 2.08 ms against 2.62 batched at 2 each, 3.73 and 2.93 at 4; order 192: 3.98 and
+// 4.75 at 16, growing by 0.23 and 0.17 each).
+bool small_pays(const SmallFit& f, int stages, const double* delta, const double* kappa) {
+  if (f.N > kSmallOrder || stages > kSmallStages) return false;
+  const int run = small_run(stages, f.cols, f.same);
+  const int64_t rounds = ceil_div(ceil_div(f.cols, run), 256) * (run > 1 ? 2 : 1);
+  if (f.loss == KMP_LOGISTIC) return f.N <= 128 || rounds <= (f.N <= 192 ? 24 : 2);
+  double sum = 0.0, most = 0.0;                   // iterations of a column
+  const int step = f.L / 64 + 1;
+  int count = 0;
+  for (int l = 0; l < f.L; l += step, ++count) {
+    double its = 0.0;
+    for (int st = 0; st < stages; ++st) {
+      const double zone = 1.0 / std::sqrt(delta[st]);
+      double c = std::sqrt(1.0 + 1.0 / (2.0 * f.lambdas[l] * kappa[st]));
+      if (f.loss == KMP_CHECK) c = std::min(std::max(c, 5.0 * zone), 14.0 * zone);
+      its += std::min((double)f.max_iter, 0.27 * std::max(1.0, -std::log(f.tol)) * c);
+    }
+    sum += its;
+    most = std::max(most, its);
+  }
+  sum *= (double)f.cols / count;
+  const int nr = f.N / 64 - 1;
+  const double form[] = {12.0, 110.0, 215.0, 850.0}, iter[] = {0.8, 1.1, 1.6, 3.6};
+  const double here = rounds * stages * form[nr] + std::max(0.6 * most, sum / 256.0) * iter[nr];
+  const double more = f.groups - 1;
+  const double batched = (160.0 + 13.5 * f.N) * (1.0 + 0.01 * more) +
+                         22.0 * (1.0 + 0.02 * more) * most + 0.039 * std::sqrt(f.N / 256.0) * sum;
+  return here <= batched;
 }
 
 int small_path(hipStream_t s, const PathArrays& p, const double* K, const SmallStages& st, double tol,

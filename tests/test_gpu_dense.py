@@ -139,3 +139,21 @@ def test_dense_form_is_taken_where_it_pays(loss, n, V, L, mode, taken):
     seen = dict(zip(km.KERNEL_CLASSES, r.timings.kernel_seen))
     print(seen["update"], seen["gemm_f"], r.iters.max().item())
     assert (seen["update"] > seen["gemm_f"]) == taken and seen["gemm_f"] > 0
+
+
+@pytest.mark.parametrize("loss,n,V,L,kw,taken", [
+    ("hinge", 200, 5, 10, {}, True),
+    ("check", 190, 3, 40, {}, True),
+    ("hinge", 250, 1, 2000, {"tol": 1e-2, "n_stages": 1}, False),   # the sweeps alone take longer
+    ("check", 250, 1, 2000, {"max_iter": 20}, False),
+])
+def test_small_orders_where_they_pay(loss, n, V, L, kw, taken):
+    """A fit in batched form has a factorisation, one of small orders none."""
+    from paper_2606_06742_amd import kmpath as km
+    device()
+    inp = W.small_problem(loss, n, 4, seed=n, V=max(V, 2), L=L, lam_lo=-4.0, lam_hi=0.0)
+    announce(f"small orders taken: loss={loss} n={n} L={L} {kw}")
+    r = km.PathRunner(inp["X"], inp["y"], loss, inp["sigmas"], inp["lambdas"], inp["fold_id"], V,
+                      taus=inp["taus"][:1] if loss == "check" else None, refit=V == 1, **kw)
+    assert r.run() >= 0
+    assert (r.timings.factor_ms == 0) == taken

@@ -230,14 +230,17 @@ __global__ __launch_bounds__(ST) void step_finish_kernel(const StepArrays a, dou
 }
 }  // namespace
 
-// Times in us, both ways, n by columns: 100 by 1 200 and 664, 700 by 20 1375 and
-// 3138, 1403 by 20 3290 and 7300, 1403 by 60 4830 and 7400, 2500 by 20 9.9 and 22.2
-// ms, by 60 22.8 and 22.2, 4000 by 20 41.5 and 59.5. A column costs n^3/3
-// operations at 16 TFLOP/s beyond the common chain of 0.9 n + 0.00075 n^2; the
-// factorisation of K takes 1.5 n + 0.0031 n^2 whatever the columns.
+// Times in us, both ways, n by columns: 60 by 1 129 and 397, by 450 276 and 507, by
+// 800 635 and 478; 128 by 300 657 and 755, by 600 785 and 751; 190 by 300 843 and
+// 972, by 600 1153 and 967; 256 by 300 784 and 1210; 700 by 20 1064 and 3168, by 300
+// 3221 and 3450; 1403 by 20 2995 and 7329, by 60 4086 and 7351, by 200 10.6 and 7.4
+// ms; 2000 by 60 8.5 and 12.5 ms, by 120 17.3 and 12.5; 3000 by 20 11.8 and 32.1. A
+// column costs n^3/3 operations at 16 TFLOP/s and the 1.5 us of its workgroups beyond
+// the common chain of 0.9 n + 0.00075 n^2; the factorisation of K takes 1.5 n + 0.0031
+// n^2 and next to nothing a column.
 bool step_pays(int64_t n, int C) {
   const double m = (double)n;
-  return n <= kStepMaxOrder && C * m * m / 47e6 <= 0.6 + 0.0023 * m;
+  return n <= kStepMaxOrder && C * (m * m / 47e6 + 1.5e-3) <= 0.6 + 0.0023 * m;
 }
 
 size_t step_doubles(int N, int C, int cap) {

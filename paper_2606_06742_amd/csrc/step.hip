@@ -274,8 +274,11 @@ int step_columns(hipStream_t s, const StepArrays& a, double* alpha_out, double* 
   hipLaunchKernelGGL(step_loss_kernel, dim3((unsigned)a.C), dim3(ST), 0, s, a);
   KMP_LAUNCH_CHECK();
   const size_t lds = 2 * sizeof(double) * a.N;
+  // (the largest at every call: the attribute is the process's, and calls of other
+  // threads may have other sizes)
   for (const void* k : {(const void*)step_solve_kernel<false>, (const void*)step_solve_kernel<true>})
-    KMP_HIP_TRY(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    KMP_HIP_TRY(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    (int)(2 * sizeof(double) * kStepMaxOrder)));
   for (int c0 = 0; c0 < a.C; c0 += a.cap) {
     const int cols = std::min(a.cap, a.C - c0);
     for (int J = 0; J < a.N / 64; ++J)

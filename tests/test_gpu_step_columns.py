@@ -95,3 +95,45 @@ def test_step_from_a_state_that_is_not_finite():
     (a0, b0), (a1, b1) = out
     assert np.array_equal(a0[[0, 2]], a1[[0, 2]]) and np.array_equal(b0[[0, 2]], b1[[0, 2]])
     assert np.array_equal(a1[1], a_in[1].cpu().numpy()) and np.isnan(b1[1])
+
+
+def test_step_from_two_threads():
+    """Steps of different orders, so of different LDS sizes, at the same time: each
+    thread's results are those of its calls alone."""
+    import threading
+
+    import torch
+    from paper_2606_06742_amd import kmpath as km
+    dev = device()
+    announce("kmp_path_step: two threads, orders 64 and 1024")
+
+    def make(n, C):
+        rng = np.random.default_rng(n)
+        X = rng.standard_normal((n, 3))
+        t = lambda a: torch.as_tensor(np.ascontiguousarray(a), dtype=torch.float64, device=dev)
+        return dict(K=t(OG.rbf_gram(X, X, 1.5)), y=t(np.where(X[:, 0] > 0, 1.0, -1.0)),
+                    lam=np.linspace(0.01, 1.0, C), a=t(rng.uniform(-1, 1, (C, n)) / n),
+                    b=t(rng.uniform(-1, 1, C)))
+
+    def step(p):
+        a, b = torch.empty_like(p["a"]), torch.empty_like(p["b"])
+        km.kmp_path_step("hinge", 0.125, p["K"], p["y"], p["lam"], p["a"], p["b"], a, b)
+        return a.cpu().numpy(), b.cpu().numpy()
+
+    problems = [make(64, 4), make(1024, 2)]
+    alone = [step(p) for p in problems]
+    got = [[], []]
+    def work(i):
+        try:
+            for _ in range(12):
+                got[i].append(step(problems[i]))
+        except Exception as e:                   # seen below
+            got[i].append(e)
+    threads = [threading.Thread(target=work, args=(i,)) for i in (0, 1)]
+    [t.start() for t in threads]
+    [t.join() for t in threads]
+    for i in (0, 1):
+        assert len(got[i]) == 12
+        for r in got[i]:
+            assert not isinstance(r, Exception), r
+            assert np.array_equal(r[0], alone[i][0]) and np.array_equal(r[1], alone[i][1])

@@ -1114,7 +1114,7 @@ int kmp_fit_path(void* stream, const kmp_path_spec* spec, const double* X, int64
       int active = Gb * C, most = 0;
       for (bool begin = true; active > 0; begin = false) {
         if ((rc = small_path(s, pa, lay.A, ss, spec->tol, spec->max_iter, restart, kSmallChunk,
-                             begin, L)) != 0)
+                             active, begin, L)) != 0)
           return rc;
         if (begin && (rc = first_checks()) != 0) return rc;
         KMP_HIP_TRY(hipMemcpyAsync(poll.p, lay.active, 2 * sizeof(int), hipMemcpyDeviceToHost, s));

@@ -274,7 +274,8 @@ int dense_check(hipStream_t s, const PathArrays& p, const DenseArrays& a, int co
 // Small orders (small.hip): every column through all smoothing stages in one
 // launch, at most count iterations of it, from K (G x N x N) without a
 // factorisation; ahat and abar hold alpha and its extrapolation in observation
-// space. begin: the first launch (flags 0, ahat 0). Columns that count stops
+// space. begin: the first launch (flags 0, ahat 0), active: the columns with flag 0.
+// Columns that count stops
 // stay active for a further launch; flag 4 marks one whose carried f would not
 // settle on K alpha or is not finite. active_count then holds the active columns
 // and the largest iters_total of any (the largest int if one has flag 4).
@@ -293,7 +294,7 @@ struct SmallFit {
 };
 bool small_pays(const SmallFit& f, int stages, const double* delta, const double* kappa);
 int small_path(hipStream_t s, const PathArrays& p, const double* K, const SmallStages& st, double tol,
-               int max_iter, int restart, int count, bool begin, int L);
+               int max_iter, int restart, int count, int64_t active, bool begin, int L);
 // One step of the path on a caller's K by a Cholesky factor per column
 // (step.hip, its tiles in dgemm.hip). Rows padded to N = 64 nb; column c's
 // factor G of M = 2 lambda I + K/(n kappa) is kept as N x N row-major lower

@@ -582,7 +582,7 @@ bool small_pays(const SmallFit& f, int stages, const double* delta, const double
 }
 
 int small_path(hipStream_t s, const PathArrays& p, const double* K, const SmallStages& st, double tol,
-               int max_iter, int restart, int count, bool begin, int L) {
+               int max_iter, int restart, int count, int64_t active, bool begin, int L) {
   const int64_t cols = (int64_t)p.G * p.C;
   const int run = small_run(st.n, cols, p.C / L);
   const unsigned blocks = (unsigned)ceil_div(cols, run);
@@ -602,10 +602,13 @@ int small_path(hipStream_t s, const PathArrays& p, const double* K, const SmallS
 #undef KMP_SMALL_CASES
 #undef KMP_SMALL_CASE
   KMP_LAUNCH_CHECK();
-  // K read once per column and its vectors; the sweeps' flops (the count of
-  // iterations is not known here)
+  // K read once and the sweeps for each resolvent formed (two at most in a run, one
+  // a column and stage otherwise), and the columns' vectors; the products of the
+  // iterations, whose number is not known here, are not counted
   const double n = (double)p.N;
-  kc_end(KMP_KC_UPDATE, s, 8.0 * cols * (n * n + 6.0 * n), 2.0 * cols * st.n * n * n * n);
+  const double formed = run > 1 ? (double)std::min<int64_t>(active, 2 * (int64_t)blocks)
+                                : (double)active * (begin ? st.n : 1);
+  kc_end(KMP_KC_UPDATE, s, 8.0 * (formed * n * n + 6.0 * active * n), 2.0 * formed * n * n * n);
   hipLaunchKernelGGL(small_report_kernel, dim3(1), dim3(1024), 0, s, cols, p.flag, p.iters_total,
                      p.active_count);
   KMP_LAUNCH_CHECK();

@@ -201,301 +201,301 @@ __global__ __launch_bounds__(DT) void small_path_kernel(const PathArrays p,
       *coef = (*next - 1.0) / (0.5 * (1.0 + sqrt(1.0 + 4.0 * *next * *next)));
     };
 
-  int stage = begin ? 0 : (int)p.gcoef[gc];
-  int it = begin ? 0 : p.iters[gc], total = begin ? 0 : p.iters_total[gc];
-  bool fresh = begin != 0;                        // a stage starts: r = 1, abar = alpha
-  double beta = p.beta[gc], bb = p.bbar[gc], rm = p.rmom[gc], kkt = 0.0;
-  const double ylab = p.ylab[(int64_t)g * N + i];
-  if (own) mine(1) = p.ahat[row];
-  double ab = p.abar[row];
-  int left = count, fl = 0, refreshes = 0;
-  for (;;) {
-    const double delta = st.delta[stage], kappa = st.kappa[stage];
-    const double nk = nvd * kappa, inv = 1.0 / nvd, i2d = 0.5 / delta;
-    if (g != hg || lam2 != hl || nk != hn) {
-    hg = g;
-    hl = lam2;
-    hn = nk;
-    // M = 2 lambda I + K/(n_v kappa)
-    const double ink = 1.0 / nk;
-    // (per stage: as loop invariants the addresses and the diagonal's lane masks
-    // would take the registers of R)
-    const double* kc = kcol;
-    int dl = lane - CW * wv;                      // entry (64 q + lane, CW wv + c): dl + 64 q == c
-    asm volatile("" : "+v"(kc), "+v"(dl));
+    int stage = begin ? 0 : (int)p.gcoef[gc];
+    int it = begin ? 0 : p.iters[gc], total = begin ? 0 : p.iters_total[gc];
+    bool fresh = begin != 0;                        // a stage starts: r = 1, abar = alpha
+    double beta = p.beta[gc], bb = p.bbar[gc], rm = p.rmom[gc], kkt = 0.0;
+    const double ylab = p.ylab[(int64_t)g * N + i];
+    if (own) mine(1) = p.ahat[row];
+    double ab = p.abar[row];
+    int left = count, fl = 0, refreshes = 0;
+    for (;;) {
+      const double delta = st.delta[stage], kappa = st.kappa[stage];
+      const double nk = nvd * kappa, inv = 1.0 / nvd, i2d = 0.5 / delta;
+      if (g != hg || lam2 != hl || nk != hn) {
+        hg = g;
+        hl = lam2;
+        hn = nk;
+        // M = 2 lambda I + K/(n_v kappa)
+        const double ink = 1.0 / nk;
+        // (per stage: as loop invariants the addresses and the diagonal's lane masks
+        // would take the registers of R)
+        const double* kc = kcol;
+        int dl = lane - CW * wv;                      // entry (64 q + lane, CW wv + c): dl + 64 q == c
+        asm volatile("" : "+v"(kc), "+v"(dl));
 #pragma unroll
-    for (int c = 0; c < CR; ++c) {
-#pragma unroll
-      for (int q = 0; q < NR; ++q)
-        rr[q][c] = fma(kc[c * N + 64 * q], ink, dl + 64 * q == c ? lam2 : 0.0);
-      if (c % 4 == 3) __builtin_amdgcn_sched_barrier(0);
-    }
-#pragma unroll
-    for (int c = 0; c < CL; ++c)
-#pragma unroll
-      for (int q = 0; q < NR; ++q)
-        rl[CL * wv + c][64 * q + lane] =
-            fma(kc[(CR + c) * N + 64 * q], ink, dl + 64 * q == CR + c ? lam2 : 0.0);
-    // sweep on index pv: with d = M_pp, column a = M e_p,
-    //   M_ij -= a_i a_j / d, M_ip = M_pi = a_i / d, M_pp = -1/d,
-    // which keeps M symmetric; after all N it holds -M^{-1} (M is positive
-    // definite: no pivoting). With row and column pv set to 0 and a_p to -1
-    // the first formula gives all three. The swept column passes through xp,
-    // two slots by parity, so one barrier a sweep.
-#pragma unroll 1
-    for (int wp = 0; wp < DW; ++wp) {
-#pragma unroll 1
-      for (int pc = 0; pc < CW; ++pc) {
-        const int pv = CW * wp + pc, qp = pv >> 6;
-        const bool lp = lane == (pv & 63);
-        double* col = xp[pv & 1];
-        if (wv == wp) {
-          double d = 0.0;
-          const auto publish = [&](auto kc) {
-            constexpr int k = decltype(kc)::value;
-            if constexpr (k < CR) {
-#pragma unroll
-              for (int q = 0; q < NR; ++q) {
-                if (q == qp) d = rr[q][k];
-                col[64 * q + lane] = rr[q][k];
-                rr[q][k] = 0.0;
-              }
-            }
-          };
-          switch (pc) {
-#define KMP_PUB(k) case k: publish(std::integral_constant<int, k>()); break;
-#define KMP_PUB4(k) KMP_PUB(k) KMP_PUB(k + 1) KMP_PUB(k + 2) KMP_PUB(k + 3)
-            KMP_PUB4(0) KMP_PUB4(4) KMP_PUB4(8) KMP_PUB4(12) KMP_PUB4(16) KMP_PUB4(20)
-#undef KMP_PUB4
-#undef KMP_PUB
-            default:
-              if constexpr (CL > 0) {
-#pragma unroll
-                for (int q = 0; q < NR; ++q) {
-                  double& m = rl[CL * wv + pc - CR][64 * q + lane];
-                  if (q == qp) d = m;
-                  col[64 * q + lane] = m;
-                  m = 0.0;
-                }
-              }
-          }
-          if (lp) {
-            col[pv] = -1.0;
-            piv[pv & 1] = d;
-          }
-        }
-        if (lp) {
+        for (int c = 0; c < CR; ++c) {
 #pragma unroll
           for (int q = 0; q < NR; ++q)
-            if (q == qp) {
-#pragma unroll
-              for (int c = 0; c < CR; ++c) rr[q][c] = 0.0;
-            }
+            rr[q][c] = fma(kc[c * N + 64 * q], ink, dl + 64 * q == c ? lam2 : 0.0);
+          if (c % 4 == 3) __builtin_amdgcn_sched_barrier(0);
         }
-        if constexpr (CL > 0) {
-          if (lane < CL) rl[CL * wv + lane][pv] = 0.0;
+#pragma unroll
+        for (int c = 0; c < CL; ++c)
+#pragma unroll
+          for (int q = 0; q < NR; ++q)
+            rl[CL * wv + c][64 * q + lane] =
+                fma(kc[(CR + c) * N + 64 * q], ink, dl + 64 * q == CR + c ? lam2 : 0.0);
+        // sweep on index pv: with d = M_pp, column a = M e_p,
+        //   M_ij -= a_i a_j / d, M_ip = M_pi = a_i / d, M_pp = -1/d,
+        // which keeps M symmetric; after all N it holds -M^{-1} (M is positive
+        // definite: no pivoting). With row and column pv set to 0 and a_p to -1
+        // the first formula gives all three. The swept column passes through xp,
+        // two slots by parity, so one barrier a sweep.
+#pragma unroll 1
+        for (int wp = 0; wp < DW; ++wp) {
+#pragma unroll 1
+          for (int pc = 0; pc < CW; ++pc) {
+            const int pv = CW * wp + pc, qp = pv >> 6;
+            const bool lp = lane == (pv & 63);
+            double* col = xp[pv & 1];
+            if (wv == wp) {
+              double d = 0.0;
+              const auto publish = [&](auto kc) {
+                constexpr int k = decltype(kc)::value;
+                if constexpr (k < CR) {
+#pragma unroll
+                  for (int q = 0; q < NR; ++q) {
+                    if (q == qp) d = rr[q][k];
+                    col[64 * q + lane] = rr[q][k];
+                    rr[q][k] = 0.0;
+                  }
+                }
+              };
+              switch (pc) {
+#define KMP_PUB(k) case k: publish(std::integral_constant<int, k>()); break;
+#define KMP_PUB4(k) KMP_PUB(k) KMP_PUB(k + 1) KMP_PUB(k + 2) KMP_PUB(k + 3)
+                KMP_PUB4(0) KMP_PUB4(4) KMP_PUB4(8) KMP_PUB4(12) KMP_PUB4(16) KMP_PUB4(20)
+#undef KMP_PUB4
+#undef KMP_PUB
+                default:
+                  if constexpr (CL > 0) {
+#pragma unroll
+                    for (int q = 0; q < NR; ++q) {
+                      double& m = rl[CL * wv + pc - CR][64 * q + lane];
+                      if (q == qp) d = m;
+                      col[64 * q + lane] = m;
+                      m = 0.0;
+                    }
+                  }
+              }
+              if (lp) {
+                col[pv] = -1.0;
+                piv[pv & 1] = d;
+              }
+            }
+            if (lp) {
+#pragma unroll
+              for (int q = 0; q < NR; ++q)
+                if (q == qp) {
+#pragma unroll
+                  for (int c = 0; c < CR; ++c) rr[q][c] = 0.0;
+                }
+            }
+            if constexpr (CL > 0) {
+              if (lane < CL) rl[CL * wv + lane][pv] = 0.0;
+            }
+            __syncthreads();
+            const double rd = -1.0 / piv[pv & 1];
+            double a[NR];
+#pragma unroll
+            for (int q = 0; q < NR; ++q) a[q] = col[64 * q + lane] * rd;
+#pragma unroll
+            for (int c = 0; c < CR; c += 2) {
+              const double2 b = *reinterpret_cast<const double2*>(&col[CW * wv + c]);
+#pragma unroll
+              for (int q = 0; q < NR; ++q) {
+                rr[q][c] = fma(a[q], b.x, rr[q][c]);
+                rr[q][c + 1] = fma(a[q], b.y, rr[q][c + 1]);
+              }
+              if (CL > 0 || c % 4 == 2) __builtin_amdgcn_sched_barrier(0);
+            }
+#pragma unroll
+            for (int c = 0; c < CL; ++c) {
+              const double b = col[CW * wv + CR + c];
+#pragma unroll
+              for (int q = 0; q < NR; ++q) {
+                double& m = rl[CL * wv + c][64 * q + lane];
+                m = fma(a[q], b, m);
+              }
+            }
+          }
+        }
+#pragma unroll
+        for (int c = 0; c < CR; ++c)
+#pragma unroll
+          for (int q = 0; q < NR; ++q) rr[q][c] = -rr[q][c];
+#pragma unroll
+        for (int c = 0; c < CL; ++c)
+#pragma unroll
+          for (int q = 0; q < NR; ++q) rl[CL * wv + c][64 * q + lane] = -rl[CL * wv + c][64 * q + lane];
+        // v = R 1/(n_v kappa), K v, g = 1/(2 lambda 1'v)
+        __syncthreads();
+        if (own) ws[0][tid] = valid ? ink : 0.0;
+        __syncthreads();
+        r_times(ws[0]);
+        __syncthreads();
+        const double v = valid ? gather() : 0.0;
+        gco = 1.0 / (lam2 * sum1(valid ? v : 0.0));
+        const double kv = k_times(v);
+        if (own) {
+          mine(0) = v;
+          kvs[tid] = kv;
+        }
+      }
+      if (fresh) {
+        ab = own ? mine(1) : 0.0;
+        bb = beta;
+        rm = 1.0;
+        it = 0;
+      }
+      // (alpha = 0 where the path begins)
+      double f = begin && stage == 0 && fresh ? 0.0 : k_times(own ? mine(1) : 0.0);
+      double fb = fresh ? f : k_times(ab);
+      fresh = false;
+      bool formed = true;                           // fb is K abar itself
+      // z and w at (a, fa, b), into slot k
+      const auto residual = [&](int k, double a, double fa, double b) {
+        double z = psi_select<LOSS>(ylab, fa + b, delta, i2d, tau) * inv;
+        z = live ? z : 0.0;
+        const double w = valid ? fma(lam2, a, z) : 0.0;
+        zs[k][tid] = z;
+        ws[k][tid] = w;
+      };
+      double rn1, co1, rn0, co0, d0 = 0.0, n2 = 0.0;
+      momentum(1.0, &rn0, &co0);
+      momentum(rm, &rn1, &co1);
+      int k = 0;
+      if (own) residual(0, ab, fb, bb);
+      __syncthreads();
+      for (;;) {
+        // x = R w; the sums of z, w^2 and (K v) w by wavefronts of their own
+        r_times(ws[k]);
+        if (wv >= DW - 4 && wv < DW - 1) {
+          double s = 0.0;
+#pragma unroll
+          for (int q = 0; q < NR; ++q) {
+            const double z = zs[k][64 * q + lane], w = ws[k][64 * q + lane], v = kvs[64 * q + lane];
+            s = fma(wv == DW - 4 ? z : w, wv == DW - 4 ? 1.0 : wv == DW - 3 ? w : v, s);
+          }
+          s = fast_wave_sum(s);
+          if (lane == 0) red3[wv - (DW - 4)] = s;
         }
         __syncthreads();
-        const double rd = -1.0 / piv[pv & 1];
-        double a[NR];
-#pragma unroll
-        for (int q = 0; q < NR; ++q) a[q] = col[64 * q + lane] * rd;
-#pragma unroll
-        for (int c = 0; c < CR; c += 2) {
-          const double2 b = *reinterpret_cast<const double2*>(&col[CW * wv + c]);
-#pragma unroll
-          for (int q = 0; q < NR; ++q) {
-            rr[q][c] = fma(a[q], b.x, rr[q][c]);
-            rr[q][c + 1] = fma(a[q], b.y, rr[q][c + 1]);
+        d0 = red3[0];
+        n2 = red3[1];
+        const double tv = red3[2];
+        // the exact test only where it may hold
+        const double q2 = nvd * nvd * n2;
+        if (!(q2 > 1.000001 * (tol * tol) && q2 <= 1e280)) {
+          kkt = nvd * fmax(sqrt(n2), fabs(d0));
+          if (!(n2 == n2) || !(d0 == d0) || !(kkt <= 1e300)) fl = 4;
+          else if (kkt <= tol) {
+            if (valid) mine(1) = ab;                // certified at the extrapolated point
+            beta = bb;
+            if (formed) fl = 1;
+            else if (++refreshes > kSmallRefresh) fl = 4;
+            else {
+              f = fb = k_times(ab);
+              formed = true;
+              k = 0;
+              if (own) residual(0, ab, fb, bb);
+              __syncthreads();
+              continue;
+            }
           }
-          if (CL > 0 || c % 4 == 2) __builtin_amdgcn_sched_barrier(0);
         }
-#pragma unroll
-        for (int c = 0; c < CL; ++c) {
-          const double b = col[CW * wv + CR + c];
-#pragma unroll
-          for (int q = 0; q < NR; ++q) {
-            double& m = rl[CL * wv + c][64 * q + lane];
-            m = fma(a[q], b, m);
+        if (fl != 0 || left <= 0) break;
+        --left;
+        ++total;
+        formed = false;
+        const bool last = ++it >= max_iter;
+        const double sa = gco * (tv - d0), db = gco * (d0 - tv);
+        const double bn = bb - db, be = bn - beta;
+        double ea = 0.0, ef = 0.0;
+        if (wv < NR) {
+          const double x = gather();
+          double rd = 0.0;
+          if (valid) {
+            const double da = fma(sa, mine(0), x);
+            ab -= da;
+            fb -= fma(sa, kvs[i], nk * fma(-lam2, x, ws[k][i]));
+            ea = ab - mine(1);
+            ef = fb - f;
+            rd = da * ea;
+            mine(1) = ab;
+            f = fb;
           }
+          // both outcomes of the restart test, so that the next product waits
+          // for one barrier
+          residual(0, fma(co1, ea, ab), fma(co1, ef, fb), fma(co1, be, bn));
+          residual(1, ab, fb, bn);
+          rd = fast_wave_sum(rd);
+          if (lane == 0) red1[wv] = rd;
+        } else if (wv == DW - 1) {
+          double tn, tc;
+          momentum(rn1, &tn, &tc);
+          if (lane == 0) {
+            mom[0] = tn;
+            mom[1] = tc;
+          }
+        }
+        __syncthreads();
+        double rd = db * be;
+#pragma unroll
+        for (int j = 0; j < NR; ++j) rd += red1[j];
+        k = restart && rd > 0.0 ? 1 : 0;
+        beta = bn;
+        if (k == 0) {
+          ab = fma(co1, ea, ab);
+          fb = fma(co1, ef, fb);
+          bb = fma(co1, be, bn);
+          rm = rn1;
+          rn1 = mom[0];
+          co1 = mom[1];
+        } else {
+          bb = bn;
+          rm = 1.0;
+          rn1 = rn0;
+          co1 = co0;
+        }
+        if (last) {
+          fl = 2;
+          break;
         }
       }
+      kkt = nvd * fmax(sqrt(n2), fabs(d0));
+      if (fl == 2) {
+        // the limit has to be the column's: its residual mostly that of K alpha, and
+        // above the rounding of such a product (eps ||alpha||_2 in an f_i)
+        const double al = own && valid ? mine(1) : 0.0;
+        const double fn = k_times(al);
+        const double dz = psi_select<LOSS>(ylab, fn + beta, delta, i2d, tau) -
+                          psi_select<LOSS>(ylab, f + beta, delta, i2d, tau);
+        const double off = sqrt(sum1(live ? dz * dz : 0.0));
+        const double rnd = kEps * (LOSS == 1 ? 0.25 : i2d) * sqrt(nv * sum1(al * al));
+        if (!(off <= fmax(tol, 0.3 * kkt) && kkt > 4.0 * rnd)) fl = 4;
+      }
+      if (fl == 0 || fl == 4 || stage + 1 >= st.n) break;
+      fl = 0;
+      ++stage;                                      // converged or at max_iter: the next stage
+      fresh = true;
+      __syncthreads();
     }
-#pragma unroll
-    for (int c = 0; c < CR; ++c)
-#pragma unroll
-      for (int q = 0; q < NR; ++q) rr[q][c] = -rr[q][c];
-#pragma unroll
-    for (int c = 0; c < CL; ++c)
-#pragma unroll
-      for (int q = 0; q < NR; ++q) rl[CL * wv + c][64 * q + lane] = -rl[CL * wv + c][64 * q + lane];
-    // v = R 1/(n_v kappa), K v, g = 1/(2 lambda 1'v)
-    __syncthreads();
-    if (own) ws[0][tid] = valid ? ink : 0.0;
-    __syncthreads();
-    r_times(ws[0]);
-    __syncthreads();
-    const double v = valid ? gather() : 0.0;
-    gco = 1.0 / (lam2 * sum1(valid ? v : 0.0));
-    const double kv = k_times(v);
     if (own) {
-      mine(0) = v;
-      kvs[tid] = kv;
+      p.ahat[row] = valid ? mine(1) : 0.0;
+      p.abar[row] = valid ? ab : 0.0;
     }
+    if (tid == 0) {
+      p.gcoef[gc] = (double)stage;
+      p.beta[gc] = beta;
+      p.bbar[gc] = bb;
+      p.rmom[gc] = rm;
+      p.kkt[gc] = kkt;
+      p.iters[gc] = it;
+      p.iters_total[gc] = total;
+      p.flag[gc] = fl;
     }
-    if (fresh) {
-      ab = own ? mine(1) : 0.0;
-      bb = beta;
-      rm = 1.0;
-      it = 0;
-    }
-    // (alpha = 0 where the path begins)
-    double f = begin && stage == 0 && fresh ? 0.0 : k_times(own ? mine(1) : 0.0);
-    double fb = fresh ? f : k_times(ab);
-    fresh = false;
-    bool formed = true;                           // fb is K abar itself
-    // z and w at (a, fa, b), into slot k
-    const auto residual = [&](int k, double a, double fa, double b) {
-      double z = psi_select<LOSS>(ylab, fa + b, delta, i2d, tau) * inv;
-      z = live ? z : 0.0;
-      const double w = valid ? fma(lam2, a, z) : 0.0;
-      zs[k][tid] = z;
-      ws[k][tid] = w;
-    };
-    double rn1, co1, rn0, co0, d0 = 0.0, n2 = 0.0;
-    momentum(1.0, &rn0, &co0);
-    momentum(rm, &rn1, &co1);
-    int k = 0;
-    if (own) residual(0, ab, fb, bb);
-    __syncthreads();
-    for (;;) {
-      // x = R w; the sums of z, w^2 and (K v) w by wavefronts of their own
-      r_times(ws[k]);
-      if (wv >= DW - 4 && wv < DW - 1) {
-        double s = 0.0;
-#pragma unroll
-        for (int q = 0; q < NR; ++q) {
-          const double z = zs[k][64 * q + lane], w = ws[k][64 * q + lane], v = kvs[64 * q + lane];
-          s = fma(wv == DW - 4 ? z : w, wv == DW - 4 ? 1.0 : wv == DW - 3 ? w : v, s);
-        }
-        s = fast_wave_sum(s);
-        if (lane == 0) red3[wv - (DW - 4)] = s;
-      }
-      __syncthreads();
-      d0 = red3[0];
-      n2 = red3[1];
-      const double tv = red3[2];
-      // the exact test only where it may hold
-      const double q2 = nvd * nvd * n2;
-      if (!(q2 > 1.000001 * (tol * tol) && q2 <= 1e280)) {
-        kkt = nvd * fmax(sqrt(n2), fabs(d0));
-        if (!(n2 == n2) || !(d0 == d0) || !(kkt <= 1e300)) fl = 4;
-        else if (kkt <= tol) {
-          if (valid) mine(1) = ab;                // certified at the extrapolated point
-          beta = bb;
-          if (formed) fl = 1;
-          else if (++refreshes > kSmallRefresh) fl = 4;
-          else {
-            f = fb = k_times(ab);
-            formed = true;
-            k = 0;
-            if (own) residual(0, ab, fb, bb);
-            __syncthreads();
-            continue;
-          }
-        }
-      }
-      if (fl != 0 || left <= 0) break;
-      --left;
-      ++total;
-      formed = false;
-      const bool last = ++it >= max_iter;
-      const double sa = gco * (tv - d0), db = gco * (d0 - tv);
-      const double bn = bb - db, be = bn - beta;
-      double ea = 0.0, ef = 0.0;
-      if (wv < NR) {
-        const double x = gather();
-        double rd = 0.0;
-        if (valid) {
-          const double da = fma(sa, mine(0), x);
-          ab -= da;
-          fb -= fma(sa, kvs[i], nk * fma(-lam2, x, ws[k][i]));
-          ea = ab - mine(1);
-          ef = fb - f;
-          rd = da * ea;
-          mine(1) = ab;
-          f = fb;
-        }
-        // both outcomes of the restart test, so that the next product waits
-        // for one barrier
-        residual(0, fma(co1, ea, ab), fma(co1, ef, fb), fma(co1, be, bn));
-        residual(1, ab, fb, bn);
-        rd = fast_wave_sum(rd);
-        if (lane == 0) red1[wv] = rd;
-      } else if (wv == DW - 1) {
-        double tn, tc;
-        momentum(rn1, &tn, &tc);
-        if (lane == 0) {
-          mom[0] = tn;
-          mom[1] = tc;
-        }
-      }
-      __syncthreads();
-      double rd = db * be;
-#pragma unroll
-      for (int j = 0; j < NR; ++j) rd += red1[j];
-      k = restart && rd > 0.0 ? 1 : 0;
-      beta = bn;
-      if (k == 0) {
-        ab = fma(co1, ea, ab);
-        fb = fma(co1, ef, fb);
-        bb = fma(co1, be, bn);
-        rm = rn1;
-        rn1 = mom[0];
-        co1 = mom[1];
-      } else {
-        bb = bn;
-        rm = 1.0;
-        rn1 = rn0;
-        co1 = co0;
-      }
-      if (last) {
-        fl = 2;
-        break;
-      }
-    }
-    kkt = nvd * fmax(sqrt(n2), fabs(d0));
-    if (fl == 2) {
-      // the limit has to be the column's: its residual mostly that of K alpha, and
-      // above the rounding of such a product (eps ||alpha||_2 in an f_i)
-      const double al = own && valid ? mine(1) : 0.0;
-      const double fn = k_times(al);
-      const double dz = psi_select<LOSS>(ylab, fn + beta, delta, i2d, tau) -
-                        psi_select<LOSS>(ylab, f + beta, delta, i2d, tau);
-      const double off = sqrt(sum1(live ? dz * dz : 0.0));
-      const double rnd = kEps * (LOSS == 1 ? 0.25 : i2d) * sqrt(nv * sum1(al * al));
-      if (!(off <= fmax(tol, 0.3 * kkt) && kkt > 4.0 * rnd)) fl = 4;
-    }
-    if (fl == 0 || fl == 4 || stage + 1 >= st.n) break;
-    fl = 0;
-    ++stage;                                      // converged or at max_iter: the next stage
-    fresh = true;
-    __syncthreads();
-  }
-  if (own) {
-    p.ahat[row] = valid ? mine(1) : 0.0;
-    p.abar[row] = valid ? ab : 0.0;
-  }
-  if (tid == 0) {
-    p.gcoef[gc] = (double)stage;
-    p.beta[gc] = beta;
-    p.bbar[gc] = bb;
-    p.rmom[gc] = rm;
-    p.kkt[gc] = kkt;
-    p.iters[gc] = it;
-    p.iters_total[gc] = total;
-    p.flag[gc] = fl;
-  }
   }
 }
 

@@ -110,7 +110,12 @@ extern "C" {
                           workgroup's LDS holds: 20224 padded rows on gfx950);
                           otherwise, for padded orders up to 3072, the last
                           columns of a stage go on with their dense
-                          resolvents; results agree to rounding            */
+                          resolvents, and up to 256 every column may take its
+                          whole path in one workgroup, where either costs less
+                          and the least penalty is large enough for f to be
+                          carried (from about 7e-6 at the default tol and
+                          levels); a column is converged by the residual at
+                          K alpha in every form; results agree to rounding  */
 
 /* Kernel classes timed with HIP events when their bit is set in
  * kmp_path_spec.timing_mask (1 << class). */
@@ -254,7 +259,8 @@ int kmp_rbf_gram(void* stream, const double* X, int64_t n, int64_t d, int64_t ld
  * HIP graph capture, tight serving loops, harnesses that forbid allocation):
  * the same arguments, layout, results and errors; neither entry point
  * allocates. n must be at most 65528 (KMP_EINVAL otherwise, before any device
- * work).                                                                    */
+ * work): a limit of this entry point's first form, which kept the norms in
+ * static scratch, that callers may count on; kmp_rbf_gram has none.         */
 int kmp_rbf_gram_noalloc(void* stream, const double* X, int64_t n, int64_t d, int64_t ldx,
                          const int32_t* rows, int64_t m, const int32_t* cols, int64_t p,
                          const double* sigmas, int32_t S, double* out, int64_t ld_out);
@@ -301,6 +307,9 @@ int kmp_band_reduce(void* stream, double* A, int32_t G, int32_t N, double* Qout,
  *   alpha_out DEVICE [C][n], beta_out DEVICE [C]: the states after the step
  *   kkt_out   DEVICE [C] or NULL: n max(||Q'(z + 2 lambda alpha)||_2, |1'z|)
  *             at the given state
+ * Device scratch: up to 2 GiB of Cholesky factors and 7 C n doubles (with less
+ * memory free it goes by the band basis), or kmp_workspace_bytes of a refit
+ * without the optional part.
  * n <= 32768, C <= 65535. Synchronises `stream`; KMP_EINVAL on bad
  * arguments (nothing written), KMP_EHIP on runtime errors.                  */
 int kmp_path_step(void* stream, int32_t loss, double delta, const double* K, int64_t n,

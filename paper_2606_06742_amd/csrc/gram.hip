@@ -102,16 +102,16 @@ __device__ __forceinline__ void gram_fetch(const double* __restrict__ x, int64_t
 // 32 (w>>1)); X in slices of 16 features through two LDS stages, the next
 // slice's loads in flight during the products of the current one (no branch
 // around a load and no arithmetic on it before it is staged: rows and features
-// past the end read valid ones and are zeroed there). PAIRS: d and ldx even and X 16-byte aligned, so a row's
-// features load as pairs. SYM: rows and columns are one list, so the matrix
-// is symmetric: the tiles on and below the diagonal are computed and stored
+// past the end read valid ones and are zeroed there). PAIRS: d and ldx even and X
+// 16-byte aligned, so a row's features load as pairs. SYM: rows and columns are one
+// list, so the matrix is symmetric: the tiles on and below the diagonal are computed and stored
 // on both sides, through LDS in whole row pieces (straight from the
-// accumulators an odd leading dimension took 900 us where it now takes 615).
+// accumulators an odd leading dimension took 900 us where it now takes 590).
 // A tile's phases (index and row loads, slices, exp, stores) are short chains
 // that only other workgroups hide: four of them share a compute unit (at most
 // 128 registers); 128 x 128 and 128 x 64 tiles, which leave one to two, were
 // slower by a fifth to a half, six and eight (fewer registers) too. Three
-// bandwidths of one matrix at d = 100: order 8191 980 -> 615 us, order 8192
+// bandwidths of one matrix at d = 100: order 8191 980 -> 590 us, order 8192
 // 500 us (1.6 GB written: 240 us at the rate of a plain fill); one, 8192 at
 // d = 16: 136 us.
 template <bool PAIRS, bool SYM>

@@ -1,9 +1,11 @@
 // Small orders (up to kSmallOrder rows per group): every column's whole path in
 // one workgroup, without a factorisation.
 //
-// A column's dense resolvent R = (2 lambda I + K/(n_v kappa))^{-1} fits the
-// registers of one compute unit (the last columns in LDS at order 256). It is
-// formed there from K by symmetric sweeps and the accelerated iteration runs
+// A column's dense resolvent R = (2 lambda I + K/(n_v kappa))^{-1} is kept in the
+// registers of one compute unit, the last columns in LDS at order 256. It takes all
+// of them from order 192: 24 to 50 registers a lane are spilled there and 126 to 145
+// at 256, the rest of the state and part of R among them, which the sweeps and the
+// iterations read back. It is formed from K by symmetric sweeps and the accelerated iteration runs
 // on alpha and f = K alpha in observation space (see dense.hip for the
 // recurrence): x = R w, K x = n_v kappa (w - 2 lambda x), so neither K nor R is
 // read again until a stage ends. The smoothing stages follow one another in

@@ -309,6 +309,7 @@ __global__ __launch_bounds__(DT) void dense_update_kernel(const DenseArrays a, c
   if (t >= *a.count) return;
   const int64_t gc = a.list[t];
   if (p.flag[gc] != 0) return;                    // uniform over the block
+  const bool may = !START || a.sure[t] == 2;      // stop here: with START in a check only
   const int N = p.N, g = (int)(gc / p.C), nv = p.nv[g];
   const double lam2 = 2.0 * p.lam[gc], nvd = (double)p.cnv[gc], tau = p.tau[gc];
   const int32_t hf = p.cfold ? p.cfold[gc] : -1;
@@ -398,7 +399,7 @@ __global__ __launch_bounds__(DT) void dense_update_kernel(const DenseArrays a, c
   block_sum3(zs, n2, tv, red);
   const double kkt = nvd * fmax(sqrt(n2), fabs(zs));
   const bool bad = !(n2 == n2) || !(zs == zs) || !(kkt <= 1e300);
-  const bool done = !bad && kkt <= tol;
+  const bool done = !bad && kkt <= tol && may;
   if (done) {
 #pragma unroll
     for (int q = 0; q < RPT; ++q) {
@@ -415,7 +416,7 @@ __global__ __launch_bounds__(DT) void dense_update_kernel(const DenseArrays a, c
       p.flag[gc] = 1;
       p.beta[gc] = bb;
     }
-    if (START) a.sure[t] = done && a.sure[t] == 2;
+    if (START) a.sure[t] = done ? 1 : 0;
   }
 }
 

@@ -1176,9 +1176,12 @@ int kmp_fit_path(void* stream, const kmp_path_spec* spec, const double* X, int64
         // it: iterations of every active column
         int it = 0, dcols = 0;        // columns in dense form (0: the batched iteration)
         int since = 0, checks = 0, chunk = kDensePoll;
+        // (the stages before the last only lead to it: columns that have stopped there
+        // get their alpha back and stay so)
+        const double accept = st + 1 < nst ? HUGE_VAL : spec->tol;
         // f of the dense columns formed again: the active columns that leaves
         const auto recheck = [&](int* active) -> int {
-          int r = dense_check(s, pa, dense, dcols, delta, kappa, spec->tol);
+          int r = dense_check(s, pa, dense, dcols, delta, kappa, accept);
           if (r != 0) return r;
           int* rep = poll.p + Gb + 1;
           KMP_HIP_TRY(hipMemcpyAsync(rep, dense.count, kDenseCounts * sizeof(int),

@@ -22,7 +22,7 @@
 // stage, 4.0 here; leave-one-out, 151 rows, logistic loss: 3.2, 2.9, 0.90 ms.
 // f is carried by the recurrence, whose rounding grows as lambda shrinks (n = 180,
 // lambda = 1e-8: f said 1e-9 where K alpha said 2.5e-5). So a column stops as
-// converged only by the residual at f = K alpha formed again (K read again), and
+// converged in the last stage only by the residual at f = K alpha formed again, and
 // what stops at max_iter with another f than that goes to the batched iteration.
 #include "kmp_common.h"
 #include "kmp_kernels.h"
@@ -395,7 +395,8 @@ __global__ __launch_bounds__(DT) void small_path_kernel(const PathArrays p,
           else if (kkt <= tol) {
             if (valid) mine(1) = ab;                // certified at the extrapolated point
             beta = bb;
-            if (formed) fl = 1;
+            // (the stages before the last only lead to it, which starts from K alpha)
+            if (formed || stage + 1 < st.n) fl = 1;
             else if (++refreshes > kSmallRefresh) fl = 4;
             else {
               f = fb = k_times(ab);

@@ -8,7 +8,7 @@
 // The tiles are solved by inverted 64 x 64 triangles, which costs digits where
 // lambda is small; one refinement with the residual brings the error below that
 // of the factorisation of K (n = 1403, 20 columns, alpha: 2.2e-13 without it,
-// 6.8e-14 with it, 1.0e-13 by the factorisation of K) for 1.0 of the 3.3 ms.
+// 6.8e-14 with it, 1.0e-13 by the factorisation of K) for 0.5 of the 2.9 ms.
 #include "kmp_common.h"
 #include "kmp_kernels.h"
 
@@ -101,7 +101,7 @@ __global__ __launch_bounds__(ST) void step_loss_kernel(const StepArrays a) {
 // along it), and the result is added to x and v. Back substitution goes from
 // the last block to the first: the columns of the block over all rows below
 // it (lanes along a row of G), then G_JJ^{-T}. Bound by reading the factor
-// through one compute unit (N = 1408: 331 us, with REFINE 711).
+// through one compute unit (N = 1408: 331 us, with REFINE 445).
 template <bool REFINE>
 __global__ __launch_bounds__(SB) void step_solve_kernel(const StepArrays a, int c0) {
   extern __shared__ double sol[];                 // 2 N: the solutions

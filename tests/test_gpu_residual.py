@@ -130,3 +130,42 @@ def test_stopped_by_max_iter_means_that_many_iterations(n):
             st, it = g["status"].ravel(), g["iters"].ravel()
             print(limit, st, it, kkt)
             assert np.all(it[st == 1] == limit) and np.all(it <= limit) and np.all(st <= 1)
+
+
+@pytest.mark.parametrize("sigma,data,max_iter", [(4.0, "random", 1500), (2.0, "random", 1500)])
+def test_small_order_left_to_the_batched_form(sigma, data, max_iter):
+    """Columns of small orders whose carried f does not settle on K alpha, or that
+    stop at max_iter by another f: the fit is made in batched form."""
+    announce(f"small order left to the batched form sigma={sigma}")
+    (c, g, kkt, noise), (cb, gb, kb, _) = _fits("hinge", 200, 5, sigma, data, 0.125, [9e-7], max_iter)
+    print(c, g["iters"].ravel(), kkt, noise, cb, gb["iters"].ravel(), kb)
+    assert g["timings"]["factor_ms"] > 0
+    assert c == cb and np.array_equal(g["status"], gb["status"])
+    assert kkt[0] <= TOL + noise[0] + 10 * kb[0], (kkt, kb)
+
+
+def test_dense_columns_done_again_in_batched_form():
+    """Dense columns that stop at max_iter by another f than K alpha's: the batch is
+    done again, with the bits of a workspace without room for dense columns."""
+    from paper_2606_06742_amd import kmpath as km
+    device()
+    n, limit = 300, 2500
+    X, y = _problem("hinge", n, 5, "shift")
+    announce("dense columns done again in batched form")
+    out = []
+    for optional in (True, False):
+        r = km.PathRunner(X, y, "hinge", np.array([20.0]), np.array([2e-8]), np.zeros(n, np.int32), 1,
+                          refit=True, max_iter=limit, delta0=1.0 / 64, n_stages=1, tol=2e-6, eager=True,
+                          kernel_timing=("update", "gemm_f"))
+        if not optional:
+            spec = km.kmp_default_spec("hinge", flags=r.spec.flags | km.KMP_FLAG_GLOBAL_SOLVE)
+            r.ws_bytes = km.kmp_workspace_bytes(spec, n, 5, 1, r.fold, 1, 1, 1, 1)
+        code = r.run()
+        seen = dict(zip(km.KERNEL_CLASSES, r.timings.kernel_seen))
+        print(code, seen["update"], seen["gemm_f"])
+        out.append((code, r.results(), seen["update"] - seen["gemm_f"]))
+    (c, g, dense), (cb, gb, none) = out
+    assert dense > 0 and none == 0
+    assert c == cb == km.KMP_WMAXITER and g["iters"].ravel()[0] == limit
+    for k in ("alpha", "beta", "objective", "iters", "status"):
+        assert np.array_equal(g[k], gb[k]), k
